@@ -155,6 +155,21 @@ def test_decode_split_invariance():
     assert torch.equal(rerun.o, runs[2].o) and torch.equal(rerun.lse, runs[2].lse)
 
 
+@pytest.mark.parametrize("D", [128, 64])
+@pytest.mark.parametrize("splits", [1, 3, 5, 32, 33])
+def test_decode_live_split_counts(splits, D):
+    """Split counts around the merge's four groups of eight loads; the steps
+    cross a split boundary, so the step's own row is also a split's only key.
+    cache_len also covers the row's length bump on summary steps."""
+    announce(f"decode live splits {splits} D={D}")
+    rows = 16 * splits - 14
+    r = DecodeRun(B=2, H=4, Hkv=2, D=D, dtype="bf16", W=30, k=4, cache_rows0=rows, starts=[0, 3],
+                  steps=20, seed=41 + splits, split=16)
+    assert int(r.err.item()) == 0
+    for b in range(2):
+        r.oracle(b, set(range(20)))
+
+
 def test_decode_capacity_error():
     """A summary step into a full cache is skipped with FOCUS_ERR_CAPACITY; the
     step still attends over what is there and the length stays put."""
