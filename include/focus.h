@@ -461,6 +461,17 @@ typedef struct {
  * offsets fall outside [0, n_pos] get FOCUS_ERR_BOUNDS and a zero mean. */
 focus_status focus_fidelity(const focus_fidelity_desc* d, focus_stream_t stream);
 
+/* The same call with scratch for the sequence means: focus_fidelity gives each
+ * sequence one workgroup, which reads only a fraction of what the device can;
+ * with at least focus_fidelity_workspace(d) bytes (0 when it would not help),
+ * 4-byte aligned, long sequences are split over several, merged by a second
+ * kernel (the means differ by float32 rounding only).  With workspace NULL or
+ * smaller it is focus_fidelity.  The scratch is in use until the call's kernels
+ * end; calls that share one on overlapping streams race. */
+size_t focus_fidelity_workspace(const focus_fidelity_desc* d);
+focus_status focus_fidelity_ws(const focus_fidelity_desc* d, void* workspace, size_t workspace_bytes,
+                               focus_stream_t stream);
+
 /* ------------------------------------------------------------------------ */
 /* FOCUS adapter attention                                                   */
 /* ------------------------------------------------------------------------ */

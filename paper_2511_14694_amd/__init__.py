@@ -402,7 +402,10 @@ def focus_fidelity(p, q, input_kind: int = FOCUS_FID_LOGITS, cu_pos=None, out=No
     d.n_pos, d.vocab, d.n_seq = n_pos, vocab, n_seq
     d.p, d.q, d.out = _ptr(p), _ptr(q), _ptr(out)
     d.cu_pos, d.seq_mean, d.err = _ptr(cu_pos), _ptr(seq_mean), _ptr(err)
-    check("focus_fidelity", lib().focus_fidelity(C.byref(d), _stream(stream, p.device)))
+    # scratch for the means of long sequences
+    nb = lib().focus_fidelity_workspace(C.byref(d))
+    ws = _scratch(nb, p.device, stream) if nb > 0 else None
+    check("focus_fidelity", lib().focus_fidelity_ws(C.byref(d), _ptr(ws), nb, _stream(stream, p.device)))
     return out, seq_mean
 
 

@@ -138,6 +138,8 @@ SYMBOLS = {
     "focus_decode_sched_start": (i32, [C.POINTER(DecodeSched), p]),
     "focus_decode_next_kind": (i32, [C.POINTER(DecodeSched), p]),
     "focus_fidelity": (i32, [C.POINTER(FidelityDesc), p]),
+    "focus_fidelity_workspace": (sz, [C.POINTER(FidelityDesc)]),
+    "focus_fidelity_ws": (i32, [C.POINTER(FidelityDesc), p, sz, p]),
     "focus_gemm": (i32, [C.POINTER(GemmDesc), p]),
     "focus_adapter_attn": (i32, [C.POINTER(AdapterDesc), p]),
     "focus_adapter_layer_workspace": (sz, [C.POINTER(AdapterLayerDesc)]),

@@ -469,37 +469,156 @@ __global__ __launch_bounds__(kThreads) void fid_logits_half(focus_fidelity_desc 
   if (lane == 0) m.store(d.out + t * FOCUS_FID_N);
 }
 
-// Mean of each metric over a sequence's positions: one workgroup per
-// sequence, a fixed-order tree sum (deterministic).
-__global__ __launch_bounds__(kThreads) void fid_seq_mean(focus_fidelity_desc d) {
-  const int b = blockIdx.x;
-  __shared__ float red[FOCUS_FID_N][kThreads];
-  const int64_t t0 = d.cu_pos[b], t1 = d.cu_pos[b + 1];
-  const bool ok = t0 >= 0 && t1 >= t0 && t1 <= d.n_pos;
-  if (!ok && threadIdx.x == 0) focus::raise_err(d.err, FOCUS_ERR_BOUNDS);
-  float acc[FOCUS_FID_N] = {0.f, 0.f, 0.f, 0.f, 0.f};
-  if (ok)
-    for (int64_t t = t0 + threadIdx.x; t < t1; t += kThreads)
+// Means of the metrics over each sequence's positions: fixed-order sums
+// (deterministic for a given alignment of out and split count).  The rows of a
+// run of positions are one run of floats; LANES threads read it 16 bytes at a
+// time, eight loads in flight each, and since 4 LANES is a multiple of the five
+// metrics every element of a thread's float4 belongs to one metric for the
+// whole run.  One workgroup reads only about 50 GB/s, so with a workspace a
+// sequence is split over up to kMaxMeanSplits workgroups (fid_mean_part), whose
+// sums fid_mean_merge adds; without one, or for short sequences, fid_seq_mean
+// takes a workgroup per sequence.  Eight sequences of 125 000 positions:
+// 220 us with one workgroup of 256 threads reading five floats each, 50 us with
+// one of 1024 as here, 14 us split (10 for the parts, 4 for the merge).
+constexpr int kMaxMeanSplits = 64;
+constexpr int kMeanPerSplit = 1024;  // positions a split is worth
+
+// sum[m] of this thread over out[f0 .. f1) (floats of whole rows)
+template <int LANES>
+__device__ inline void sum_rows(const float* out, int64_t f0, int64_t f1, float (&sum)[FOCUS_FID_N]) {
+  constexpr int kUnroll = 8;
+  static_assert(4 * LANES % FOCUS_FID_N == 0, "a fixed metric per element");
+  const int tid = threadIdx.x;
 #pragma unroll
-      for (int m = 0; m < FOCUS_FID_N; ++m) acc[m] += d.out[t * FOCUS_FID_N + m];
+  for (int m = 0; m < FOCUS_FID_N; ++m) sum[m] = 0.f;
+  // [a0, a0 + 4 nv) is the 16-byte-aligned part
+  const int64_t skew = (int64_t)((reinterpret_cast<uintptr_t>(out + f0) >> 2) & 3);
+  const int64_t a0 = min(f0 + ((4 - skew) & 3), f1), nv = (f1 - a0) / 4;
+  const float4* v = reinterpret_cast<const float4*>(out + a0);
+  if (tid < LANES) {
+    float acc[4] = {0.f, 0.f, 0.f, 0.f};
+    for (int64_t i0 = tid; i0 < nv; i0 += (int64_t)LANES * kUnroll) {
+      float4 x[kUnroll];
 #pragma unroll
-  for (int m = 0; m < FOCUS_FID_N; ++m) red[m][threadIdx.x] = acc[m];
+      for (int u = 0; u < kUnroll; ++u) x[u] = v[min(i0 + (int64_t)u * LANES, nv - 1)];
+#pragma unroll
+      for (int u = 0; u < kUnroll; ++u) {
+        const bool in = i0 + (int64_t)u * LANES < nv;  // past the end: the last one again, added as zero
+        acc[0] += in ? x[u].x : 0.f;
+        acc[1] += in ? x[u].y : 0.f;
+        acc[2] += in ? x[u].z : 0.f;
+        acc[3] += in ? x[u].w : 0.f;
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int m = 0; m < FOCUS_FID_N; ++m)
+        if ((a0 + 4 * tid + j) % FOCUS_FID_N == m) sum[m] = acc[j];
+  } else if (tid == LANES) {
+    // the floats before and after the aligned part
+    const int64_t head = a0 - f0, edge = f1 - f0 - 4 * nv;
+    for (int64_t i = 0; i < edge; ++i) {
+      const int64_t f = i < head ? f0 + i : a0 + 4 * nv + (i - head);
+#pragma unroll
+      for (int m = 0; m < FOCUS_FID_N; ++m)
+        if (f % FOCUS_FID_N == m) sum[m] += out[f];
+    }
+  }
+}
+
+// The workgroup's sums of metric m in thread m < FOCUS_FID_N.
+template <int THREADS>
+__device__ inline float block_sums(const float (&sum)[FOCUS_FID_N]) {
+  __shared__ float red[FOCUS_FID_N][THREADS / 64];
+  const int tid = threadIdx.x;
+#pragma unroll
+  for (int m = 0; m < FOCUS_FID_N; ++m) {
+    const float x = wave_sum(sum[m]);
+    if ((tid & 63) == 0) red[m][tid >> 6] = x;
+  }
   __syncthreads();
-  for (int s = kThreads / 2; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s)
+  float x = 0.f;
+  if (tid < FOCUS_FID_N)
 #pragma unroll
-      for (int m = 0; m < FOCUS_FID_N; ++m) red[m][threadIdx.x] += red[m][threadIdx.x + s];
-    __syncthreads();
+    for (int w = 0; w < THREADS / 64; ++w) x += red[tid][w];
+  return x;
+}
+
+// Positions [t0, t1) of sequence b; false (nothing to read) if out of range.
+__device__ inline bool seq_range(const focus_fidelity_desc& d, int b, int64_t& t0, int64_t& t1) {
+  t0 = d.cu_pos[b];
+  t1 = d.cu_pos[b + 1];
+  return t0 >= 0 && t1 >= t0 && t1 <= d.n_pos;
+}
+
+constexpr int kMeanThreads = 1024, kMeanLanes = 1020;
+__global__ __launch_bounds__(kMeanThreads) void fid_seq_mean(focus_fidelity_desc d) {
+  const int b = blockIdx.x, tid = threadIdx.x;
+  int64_t t0, t1;
+  const bool ok = seq_range(d, b, t0, t1);
+  if (!ok) {
+    t0 = t1 = 0;
+    if (tid == 0) focus::raise_err(d.err, FOCUS_ERR_BOUNDS);
   }
-  if ((int)threadIdx.x < FOCUS_FID_N) {
-    const int64_t n = ok ? t1 - t0 : 0;
-    d.seq_mean[(int64_t)b * FOCUS_FID_N + threadIdx.x] = n > 0 ? red[threadIdx.x][0] / (float)n : 0.f;
+  float sum[FOCUS_FID_N];
+  sum_rows<kMeanLanes>(d.out, t0 * FOCUS_FID_N, t1 * FOCUS_FID_N, sum);
+  const float x = block_sums<kMeanThreads>(sum);
+  if (tid < FOCUS_FID_N) d.seq_mean[(int64_t)b * FOCUS_FID_N + tid] = t1 > t0 ? x / (float)(t1 - t0) : 0.f;
+}
+
+// Split s of sequence b: its share of the positions, summed into
+// ws[b][s][metric].  Block b * n_split + s.
+constexpr int kPartThreads = 256, kPartLanes = 250;
+__global__ __launch_bounds__(kPartThreads) void fid_mean_part(focus_fidelity_desc d, int n_split, float* ws) {
+  const int b = blockIdx.x / n_split, s = blockIdx.x % n_split, tid = threadIdx.x;
+  int64_t t0, t1;
+  if (!seq_range(d, b, t0, t1)) {
+    t0 = t1 = 0;
+    if (s == 0 && tid == 0) focus::raise_err(d.err, FOCUS_ERR_BOUNDS);
   }
+  const int64_t n = t1 - t0, u0 = t0 + n * s / n_split, u1 = t0 + n * (s + 1) / n_split;
+  float sum[FOCUS_FID_N];
+  sum_rows<kPartLanes>(d.out, u0 * FOCUS_FID_N, u1 * FOCUS_FID_N, sum);
+  const float x = block_sums<kPartThreads>(sum);
+  if (tid < FOCUS_FID_N) ws[(int64_t)blockIdx.x * FOCUS_FID_N + tid] = x;
+}
+
+// One wave per sequence: lane s holds split s.
+__global__ __launch_bounds__(64) void fid_mean_merge(focus_fidelity_desc d, int n_split, const float* ws) {
+  const int b = blockIdx.x, lane = threadIdx.x;
+  int64_t t0, t1;
+  const int64_t n = seq_range(d, b, t0, t1) ? t1 - t0 : 0;
+#pragma unroll
+  for (int m = 0; m < FOCUS_FID_N; ++m) {
+    const float x = wave_sum(lane < n_split ? ws[((int64_t)b * n_split + lane) * FOCUS_FID_N + m] : 0.f);
+    if (lane == 0) d.seq_mean[(int64_t)b * FOCUS_FID_N + m] = n > 0 ? x / (float)n : 0.f;
+  }
+}
+
+// Splits per sequence: what the mean length is worth, at most kMaxMeanSplits.
+int mean_splits(const focus_fidelity_desc* d) {
+  if (d->n_seq <= 0 || !d->seq_mean) return 1;
+  const int64_t n = d->n_pos / d->n_seq / kMeanPerSplit;
+  return (int)(n < 2 ? 1 : n > kMaxMeanSplits ? kMaxMeanSplits : n);
+}
+
+size_t mean_bytes(const focus_fidelity_desc* d, int n_split) {
+  return n_split < 2 ? 0 : (size_t)d->n_seq * n_split * FOCUS_FID_N * sizeof(float);
 }
 
 }  // namespace
 
+extern "C" size_t focus_fidelity_workspace(const focus_fidelity_desc* d) {
+  return d ? mean_bytes(d, mean_splits(d)) : 0;
+}
+
 extern "C" focus_status focus_fidelity(const focus_fidelity_desc* d, focus_stream_t stream) {
+  return focus_fidelity_ws(d, nullptr, 0, stream);
+}
+
+extern "C" focus_status focus_fidelity_ws(const focus_fidelity_desc* d, void* workspace, size_t workspace_bytes,
+                                          focus_stream_t stream) {
   if (!d) return FOCUS_E_NULL;
   if (d->dtype != FOCUS_BF16 && d->dtype != FOCUS_F32) return FOCUS_E_DTYPE;
   if (d->input_kind != FOCUS_FID_LOGITS && d->input_kind != FOCUS_FID_PROBS) return FOCUS_E_ARG;
@@ -562,7 +681,17 @@ extern "C" focus_status focus_fidelity(const focus_fidelity_desc* d, focus_strea
     if (st != FOCUS_OK) return st;
   }
   if (want_mean) {
-    hipLaunchKernelGGL(fid_seq_mean, dim3(d->n_seq), dim3(kThreads), 0, s, *d);
+    const int ns = mean_splits(d);
+    if (ns > 1 && workspace && (reinterpret_cast<uintptr_t>(workspace) & 3u) == 0 &&
+        workspace_bytes >= mean_bytes(d, ns) && (int64_t)d->n_seq * ns <= INT32_MAX / kPartThreads) {
+      float* ws = reinterpret_cast<float*>(workspace);
+      hipLaunchKernelGGL(fid_mean_part, dim3((uint32_t)(d->n_seq * ns)), dim3(kPartThreads), 0, s, *d, ns, ws);
+      focus_status st = focus::launch_status();
+      if (st != FOCUS_OK) return st;
+      hipLaunchKernelGGL(fid_mean_merge, dim3(d->n_seq), dim3(64), 0, s, *d, ns, ws);
+      return focus::launch_status();
+    }
+    hipLaunchKernelGGL(fid_seq_mean, dim3(d->n_seq), dim3(kMeanThreads), 0, s, *d);
     return focus::launch_status();
   }
   return FOCUS_OK;

@@ -9,6 +9,8 @@ inputs): |got - ref| <= 2e-5 + 2e-5 |ref| per metric; identical inputs give
 exact zeros.
 """
 
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -16,6 +18,7 @@ import torch
 import focus_workloads as fw
 import paper_2511_14694_amd as F
 from gpu_util import DEV, announce, to64
+from paper_2511_14694_amd import _abi
 from oracle import fidelity as FD
 
 pytestmark = pytest.mark.gpu
@@ -95,6 +98,28 @@ def test_empty_and_bounds():
     assert (mean[1] == 0).all()
     ref = FD.metrics_from_logits(to64(x), to64(y))
     _check(mean[0].cpu().numpy().astype(np.float64), ref[:4].mean(0), "mean of a valid sequence")
+
+
+@pytest.mark.parametrize("cu", [[0, 2047, 4096], [1, 3, 4000, 9001], [0, 0, 5001, 5001, 8191], [5, 130_003]])
+def test_sequence_means_split(cu):
+    """Means of sequences that start at every 16-byte phase of the output rows,
+    empty, shorter and longer than a split; with and without the split, against
+    the float64 mean of the device's own rows (sums of n float32: n 2^-24)."""
+    announce(f"fidelity split means {cu}")
+    n = cu[-1] + 2
+    p, q = fw.fidelity_logits(n, 4, "f32", seed=n, device=DEV)
+    out, mean = F.focus_fidelity(p, q, cu_pos=cu)
+    d = _abi.FidelityDesc()
+    single = torch.empty_like(mean)
+    cu_d = torch.as_tensor(cu, dtype=torch.int64, device=DEV)
+    d.dtype, d.n_pos, d.vocab, d.n_seq = _abi.FOCUS_F32, n, 4, len(cu) - 1
+    d.p, d.q, d.out, d.cu_pos, d.seq_mean = (t.data_ptr() for t in (p, q, out, cu_d, single))
+    assert _abi.lib().focus_fidelity_workspace(C.byref(d)) > 0
+    assert _abi.lib().focus_fidelity(C.byref(d), torch.cuda.current_stream().cuda_stream) == 0
+    torch.cuda.synchronize()
+    ref = FD.sequence_means(out.cpu().numpy().astype(np.float64), np.asarray(cu))
+    for got in (mean, single):
+        np.testing.assert_allclose(got.cpu().numpy(), ref, rtol=2e-6, atol=1e-9)
 
 
 @pytest.mark.parametrize("name", list(fw.FIDELITY))
