@@ -23,9 +23,10 @@
 //                 max / row sum are lane-local plus one exchange with lane^32;
 //                 the next sub-tile's scores are issued on the MFMA pipe while
 //                 the VALU does this sub-tile's softmax;
-//   softmax       exp2 domain, running max with lazy rescaling: the output
-//                 accumulator is rescaled only when a row's max grows by more
-//                 than 2^8, which keeps exp2 arguments <= 8 and is exact;
+//   softmax       exp2 domain, running reference with lazy rescaling: the row
+//                 maximum is taken and the output accumulator rescaled only when
+//                 a lane's 16 probabilities sum to more than 2^12, which is exact
+//                 (numerator and denominator share the reference);
 //   O^T += V^T P^T  the same MFMA; P comes straight from the S^T accumulator
 //                 (rounded to bf16), V^T is read from LDS with the gfx950
 //                 transposing read ds_read_b64_tr_b16.
@@ -64,6 +65,7 @@ constexpr float kLn2 = 0.69314718055994531f;
 constexpr float kLog2e = 1.44269504088896341f;
 constexpr float kMinit = -1.0e30f;  // finite start of the running max (no inf - inf)
 constexpr float kLazy = 8.0f;       // rescale when the max grows by > 2^8
+constexpr float kLazySum = 4096.f;  // ... or when a lane's 16 probabilities sum to > 2^12
 
 typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
 typedef __attribute__((address_space(3))) void lds_void;
@@ -986,6 +988,15 @@ __global__ __launch_bounds__(64 * W, 8 / W) void attn_kl(focus_attn_desc d, floa
   __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));  // vmcnt(0)
 }
 
+// Row maximum of a lane's 16 scores and those of lane ^ 32 (the row's other half).
+__device__ __forceinline__ float row_max(const f32x16& s) {
+  float mx = s[0];
+#pragma unroll
+  for (int v = 1; v < 16; ++v) mx = fmaxf(mx, s[v]);
+  const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+  return fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+}
+
 // ------------------------------------------- bf16 MFMA, C(t), pipelined waves
 
 // The C(t) window attention: one workgroup = 8 waves x 32 query rows of one
@@ -1232,6 +1243,8 @@ __global__ __launch_bounds__(512, 2) void attn_ct(
       for (int i = 0; i < C::kDma; ++i)
         if ((i & 1) == half) issue(src, kcp, vcp, i, !fast && !src.full);
     }
+    // K operands of sub-tile j + 2
+    read_k(kn, half);
     if (lj) {
       f32x16& s = sacc[half];
       const int J = J0 + j;
@@ -1249,15 +1262,25 @@ __global__ __launch_bounds__(512, 2) void attn_ct(
             if ((v >> 2) * 8 + (v & 3) > lim_g) s[v] = -INFINITY;
         }
       }
-      float mx = s[0];
+      // The probabilities against the running reference; their sum, which the
+      // row sum needs anyway, says whether the reference is still high enough
+      // (numerator and denominator use the same one, so any is exact).  A row
+      // maximum per sub-tile cost 15 of 75 vector instructions and sat between
+      // the scores and the exponentials: 1 Mb 88.5 -> 87.0 ms, 100 kb 2.28 -> 2.25.
+      bf16x8 pb[2];
+      float psum;
+      auto probs = [&]() __attribute__((always_inline)) {
+        psum = 0.f;
 #pragma unroll
-      for (int v = 1; v < 16; ++v) mx = fmaxf(mx, s[v]);
-      {
-        const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
-        mx = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));  // with lane ^ 32
-      }
-      const float m_new = fmaxf(m_run, mx * sc);
-      if (__any(m_new - m_run > kLazy)) {
+        for (int v = 0; v < 16; ++v) {
+          const float p = __builtin_amdgcn_exp2f(fmaf(s[v], sc, -m_run));
+          psum += p;
+          pb[v >> 3][v & 7] = (__bf16)p;
+        }
+      };
+      probs();
+      if (__any(psum > kLazySum)) {
+        const float m_new = fmaxf(m_run, row_max(s) * sc);
         const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
         l_run *= alpha;
 #pragma unroll
@@ -1265,29 +1288,14 @@ __global__ __launch_bounds__(512, 2) void attn_ct(
 #pragma unroll
           for (int v = 0; v < 16; ++v) oacc[dt][v] *= alpha;
         m_run = m_new;
-      }
-    }
-    // K operands of sub-tile j + 2
-    read_k(kn, half);
-    if (lj) {
-      f32x16& s = sacc[half];
-      float psum = 0.f;
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const float p = __builtin_amdgcn_exp2f(fmaf(s[v], sc, -m_run));
-        s[v] = p;
-        psum += p;
+        probs();
       }
       l_run += psum;
 #pragma unroll
-      for (int m = 0; m < 2; ++m) {
-        bf16x8 pb;
-#pragma unroll
-        for (int v = 0; v < 8; ++v) pb[v] = (__bf16)s[8 * m + v];
+      for (int m = 0; m < 2; ++m)
 #pragma unroll
         for (int dt = 0; dt < C::kDtiles; ++dt)
-          oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vop[m * C::kDtiles + dt], pb, oacc[dt], 0, 0, 0);
-      }
+          oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vop[m * C::kDtiles + dt], pb[m], oacc[dt], 0, 0, 0);
     }
   };
 
