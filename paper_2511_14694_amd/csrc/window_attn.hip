@@ -48,8 +48,9 @@
 // summaries share one workgroup (attn_sq_block); otherwise the bf16 kernel
 // above runs with one wave of 32 summary slots per (window, head).
 //
-// f32 path: a plain VALU kernel (4 lanes per query row, exact online softmax),
-// used for the float32 checks; it is not tuned.
+// f32 path (attn_f32): float32 MFMAs and exact online softmax, 16 query rows per
+// workgroup with the keys dealt to its waves, for the float32 checks of short
+// sequences.
 #include "common.h"
 
 #include <math.h>
@@ -59,6 +60,7 @@ namespace {
 using focus::bf16x4;
 using focus::bf16x8;
 using focus::f32x16;
+using focus::f32x4;
 using focus::u32x4;
 
 constexpr float kLn2 = 0.69314718055994531f;
@@ -78,6 +80,9 @@ constexpr int kBf16WavesKL = 4;
 // attn_kl at head_dim 128: waves per workgroup and LDS stages (8 waves and 8
 // stages, one workgroup per CU: 8.41 vs 7.86 ms at 1 Mb)
 constexpr int kKlWaves128 = 4, kKlStages128 = 4;
+
+// attn_f32: query rows per workgroup, waves its keys are dealt to
+constexpr int kF32Rows = 16, kF32Waves = 4;
 
 struct Item {
   int64_t list_idx;
@@ -1893,16 +1898,33 @@ __global__ __launch_bounds__(256) void attn_combine(focus_attn_desc d, Split sp)
   if (c == 0 && d.lse) d.lse[orow * H + h] = (mx + log2f(l)) * kLn2;
 }
 
-// ----------------------------------------------------------------- f32 VALU
+// ----------------------------------------------------------------- f32 MFMA
 
+// float32 attention, everything in float32 (v_mfma_f32_16x16x4_f32).  The calls
+// it serves are short sequences of a few heads, bound by the length of the
+// serial chain over a row's keys and by how many waves there are: 16 query rows
+// per workgroup, whose waves take the 16 kT-key blocks in turn and merge
+// (max, sum, output) through LDS.  Operands go from memory (L2) to registers,
+// the next block's while one is computed:
+//   S^T = K Q^T    lane (l % 16, g = l / 16) holds key (query) l % 16 at
+//                  head_dim 16 i + 4 g + c in k-step (i, c), so a row's 64
+//                  bytes are read together;
+//   O^T = V^T P^T  the scores of a lane are keys 4 g + r of query l % 16; k-step
+//                  r takes those keys, and output block 4 f + c is head_dim
+//                  64 f + 4 row + c, so V and O move 16 bytes a lane.
+// 4 kb, one head of 64: 248 us with 4 lanes per query row and one key at a time
+// on the vector unit, 30 us now; 16 kb, 4 heads of 128 run at 60 TFLOP/s
+// (0.36 ms).  8 waves per workgroup: the same for one head, 0.46 ms for four.
 template <int D, bool KL>
-__global__ __launch_bounds__(256) void attn_f32(focus_attn_desc d, float sc, int64_t n_pairs, int QT, SumQ) {
-  constexpr int kBQ = 64, kBK = 32, kF4 = D / 4, kPer = D / 16;  // float4 per row / per lane
-  __shared__ float4 ks[kBK][kF4];
-  __shared__ float4 vs[kBK][kF4];
+__global__ __launch_bounds__(64 * kF32Waves, D == 64 ? 2 : 1) void attn_f32(focus_attn_desc d, float sc, int64_t n_pairs, int QT) {
+  constexpr int kT = 128 / D;              // 16-key tiles per block
+  constexpr int kI = D / 16, kF = D / 64;  // 16-byte pieces of a lane's K row part, of its V row part
+  constexpr int kWv = kF32Waves;
+  __shared__ float4 po[kWv][kF32Rows][D / 4];
+  __shared__ float pm[kWv][kF32Rows], pl[kWv][kF32Rows];
 
-  const int tid = threadIdx.x;
-  const Item it = map_block(blockIdx.x, n_pairs, d.n_heads, QT);
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, c16 = lane & 15, g = lane >> 4;
+  const Item it = map_block((int64_t)blockIdx.y * gridDim.x + blockIdx.x, n_pairs, d.n_heads, QT);
   if (!it.valid) return;
   const int64_t gw = listed_window(d, it.list_idx);
   if (gw < 0 || gw >= d.totals.n_windows) {
@@ -1910,7 +1932,7 @@ __global__ __launch_bounds__(256) void attn_f32(focus_attn_desc d, float sc, int
     return;
   }
   const int T = d.win_ntok[gw];
-  const int q0 = it.qt * kBQ;
+  const int q0 = it.qt * kF32Rows;
   if (q0 >= T) return;
   const int Cw = d.win_cache_off[gw];
   const int b = d.win_seq[gw];
@@ -1921,8 +1943,8 @@ __global__ __launch_bounds__(256) void attn_f32(focus_attn_desc d, float sc, int
   }
   const int H = d.n_heads, Hkv = d.n_kv_heads, h = it.h;
   const int hk = h / (H / Hkv);
-  const int nkeys = Cw + min(T, q0 + kBQ);
-  const int qi = q0 + (tid >> 2), sub = tid & 3;
+  const int nkeys = Cw + min(T, q0 + kF32Rows);
+  const int qi = q0 + c16;
   int kw = 0;
   if constexpr (KL) {
     kw = d.win_kmer ? d.win_kmer[gw] : d.kmer_uniform;
@@ -1941,82 +1963,194 @@ __global__ __launch_bounds__(256) void attn_f32(focus_attn_desc d, float sc, int
     const bool summary = u % (kw + 1) == kw || u == T - 1;
     return summary || u / (kw + 1) == qi / (kw + 1);
   };
-  const int64_t row_f4 = (int64_t)Hkv * kF4;
+  const int64_t row_f4 = (int64_t)Hkv * (D / 4);
+  const float4* kwin = reinterpret_cast<const float4*>(d.k) + tok0 * row_f4 + hk * (D / 4);
+  const float4* vwin = reinterpret_cast<const float4*>(d.v) + tok0 * row_f4 + hk * (D / 4);
+  const float4* kcache = reinterpret_cast<const float4*>(d.cache_k) + (int64_t)b * d.cache_cap * row_f4 + hk * (D / 4);
+  const float4* vcache = reinterpret_cast<const float4*>(d.cache_v) + (int64_t)b * d.cache_cap * row_f4 + hk * (D / 4);
 
-  float4 qv[kPer], ov[kPer];
+  f32x4 qv[kI];
   {
-    const float4* qp = reinterpret_cast<const float4*>(d.q) + (tok0 + min(qi, T - 1)) * H * kF4 + h * kF4;
+    const f32x4* qp = reinterpret_cast<const f32x4*>(d.q) + ((tok0 + min(qi, T - 1)) * H + h) * (D / 4) + g;
 #pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-      qv[i] = qp[4 * i + sub];
-      ov[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-    }
+    for (int i = 0; i < kI; ++i) qv[i] = qp[4 * i];
   }
-  const float4* kwin = reinterpret_cast<const float4*>(d.k) + tok0 * row_f4 + hk * kF4;
-  const float4* vwin = reinterpret_cast<const float4*>(d.v) + tok0 * row_f4 + hk * kF4;
-  const float4* kcache = reinterpret_cast<const float4*>(d.cache_k) + (int64_t)b * d.cache_cap * row_f4 + hk * kF4;
-  const float4* vcache = reinterpret_cast<const float4*>(d.cache_v) + (int64_t)b * d.cache_cap * row_f4 + hk * kF4;
+  struct Block {
+    f32x4 k[kT][kI], v[kT][4][kF];
+  };
+  // rows past the last key repeat it (they are masked)
+  auto load = [&](int jb, Block& x) __attribute__((always_inline)) {
+#pragma unroll
+    for (int t = 0; t < kT; ++t) {
+      const int j = min(16 * (kT * jb + t) + c16, nkeys - 1);
+      const f32x4* kp = reinterpret_cast<const f32x4*>(j < Cw ? kcache + j * row_f4 : kwin + (j - Cw) * row_f4) + g;
+#pragma unroll
+      for (int i = 0; i < kI; ++i) x.k[t][i] = kp[4 * i];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int jv = min(16 * (kT * jb + t) + 4 * g + r, nkeys - 1);
+        const f32x4* vp = reinterpret_cast<const f32x4*>(jv < Cw ? vcache + jv * row_f4 : vwin + (jv - Cw) * row_f4) + c16;
+#pragma unroll
+        for (int f = 0; f < kF; ++f) x.v[t][r][f] = vp[16 * f];
+      }
+    }
+  };
 
-  float m = kMinit, l = 0.f;
-  for (int j0 = 0; j0 < nkeys; j0 += kBK) {
-    __syncthreads();
-    for (int c = tid; c < kBK * kF4; c += 256) {
-      const int r = c / kF4, c4 = c % kF4, j = j0 + r;
-      float4 kx = make_float4(0.f, 0.f, 0.f, 0.f), vx = kx;
-      if (j < Cw) {
-        kx = kcache[(int64_t)j * row_f4 + c4];
-        vx = vcache[(int64_t)j * row_f4 + c4];
-      } else if (j < nkeys) {
-        kx = kwin[(int64_t)(j - Cw) * row_f4 + c4];
-        vx = vwin[(int64_t)(j - Cw) * row_f4 + c4];
-      }
-      ks[r][c4] = kx;
-      vs[r][c4] = vx;
-    }
-    __syncthreads();
-    const int kend = min(kBK, nkeys - j0);
-    for (int kk = 0; kk < kend; ++kk) {
-      float s = 0.f;
+  f32x4 ov[4 * kF];
 #pragma unroll
-      for (int i = 0; i < kPer; ++i) {
-        const float4 kx = ks[kk][4 * i + sub];
-        s = fmaf(qv[i].x, kx.x, s);
-        s = fmaf(qv[i].y, kx.y, s);
-        s = fmaf(qv[i].z, kx.z, s);
-        s = fmaf(qv[i].w, kx.w, s);
-      }
-      s = focus::sum4(s) * sc;
-      const int j = j0 + kk;
-      if (visible(j)) {
-        const float m_new = fmaxf(m, s);
-        const float corr = __builtin_amdgcn_exp2f(m - m_new);
-        const float p = __builtin_amdgcn_exp2f(s - m_new);
-        l = l * corr + p;
+  for (int i = 0; i < 4 * kF; ++i) ov[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float m = kMinit, l = 0.f;  // m: of the row; l: of this lane's keys
+  auto compute = [&](int jb, const Block& x) __attribute__((always_inline)) {
+    const int j0 = 16 * kT * jb;
+    f32x4 s[kT];
 #pragma unroll
-        for (int i = 0; i < kPer; ++i) {
-          const float4 vx = vs[kk][4 * i + sub];
-          ov[i].x = fmaf(p, vx.x, ov[i].x * corr);
-          ov[i].y = fmaf(p, vx.y, ov[i].y * corr);
-          ov[i].z = fmaf(p, vx.z, ov[i].z * corr);
-          ov[i].w = fmaf(p, vx.w, ov[i].w * corr);
+    for (int t = 0; t < kT; ++t) s[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < kI; ++i)
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+#pragma unroll
+        for (int t = 0; t < kT; ++t) s[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(x.k[t][i][c], qv[i][c], s[t], 0, 0, 0);
+    const bool masked = KL || j0 + 16 * kT - 1 > Cw + q0;
+    bool any = true;
+    uint32_t vmax = 0;  // largest exponent field of the block's V (all ones: an infinity or NaN)
+    if (masked) {
+      any = false;
+#pragma unroll
+      for (int t = 0; t < kT; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int j = j0 + 16 * t + 4 * g + r;
+          const bool vis = j < nkeys && visible(j);
+          any |= vis;
+          if (!vis) s[t][r] = -INFINITY;
+#pragma unroll
+          for (int f = 0; f < kF; ++f)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) vmax = max(vmax, __float_as_uint(x.v[t][r][f][c]) & 0x7f800000u);
         }
-        m = m_new;
+    }
+    if (KL && !__any(any)) return;
+    float mx = -INFINITY;
+#pragma unroll
+    for (int t = 0; t < kT; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        s[t][r] *= sc;
+        mx = fmaxf(mx, s[t][r]);
       }
+    {
+      const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+      mx = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+      const auto c = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+      mx = fmaxf(__uint_as_float(c[0]), __uint_as_float(c[1]));
+    }
+    if (__any(mx > m)) {
+      const float m_new = fmaxf(m, mx);
+      const float corr = __builtin_amdgcn_exp2f(m - m_new);
+      l *= corr;
+#pragma unroll
+      for (int i = 0; i < 4 * kF; ++i) ov[i] *= corr;
+      m = m_new;
+    }
+#pragma unroll
+    for (int t = 0; t < kT; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        s[t][r] = __builtin_amdgcn_exp2f(s[t][r] - m);
+        l += s[t][r];
+      }
+    if (masked && __any(vmax == 0x7f800000u)) {
+      // an infinity or NaN in V must not reach rows that do not see its key
+      // (0 times it is NaN): one key at a time, added where it is visible
+#pragma unroll 1
+      for (int e = 0; e < 16 * kT; ++e) {
+        const int j = j0 + 16 * (e >> 4) + 4 * (e & 3) + ((e >> 2) & 3);
+        float p = s[0][0];
+#pragma unroll
+        for (int i = 1; i < 4 * kT; ++i) p = (e >> 2) == i ? s[i / 4][i % 4] : p;
+        p = __shfl(p, 16 * (e & 3) + c16);
+        if (j < nkeys && visible(j)) {
+          const f32x4* vp = reinterpret_cast<const f32x4*>(j < Cw ? vcache + j * row_f4 : vwin + (j - Cw) * row_f4) + 4 * g;
+#pragma unroll
+          for (int f = 0; f < kF; ++f)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              const f32x4 v = vp[16 * f + r];
+#pragma unroll
+              for (int c = 0; c < 4; ++c) ov[4 * f + c][r] = fmaf(p, v[c], ov[4 * f + c][r]);
+            }
+        }
+      }
+      return;
+    }
+#pragma unroll
+    for (int t = 0; t < kT; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int i = 0; i < 4 * kF; ++i)
+          ov[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(x.v[t][r][i / 4][i % 4], s[t][r], ov[i], 0, 0, 0);
+  };
+
+  const int nb = (nkeys + 16 * kT - 1) / (16 * kT);
+  int jb = wave;
+  if (jb < nb) {
+    Block b0, b1;
+    load(jb, b0);
+    for (; jb < nb; jb += 2 * kWv) {
+      if (jb + kWv < nb) load(jb + kWv, b1);
+      compute(jb, b0);
+      if (jb + kWv >= nb) break;
+      if (jb + 2 * kWv < nb) load(jb + 2 * kWv, b0);
+      compute(jb + kWv, b1);
     }
   }
-  if (qi < T) {
-    const float inv = 1.f / l;
-    float4* op = reinterpret_cast<float4*>(d.o) + (tok0 + qi) * H * kF4 + h * kF4;
+  {
+    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(l), __float_as_uint(l), false, false);
+    l = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+    const auto c = __builtin_amdgcn_permlane32_swap(__float_as_uint(l), __float_as_uint(l), false, false);
+    l = __uint_as_float(c[0]) + __uint_as_float(c[1]);
+  }
+  // ov[4 f + c][r] = O[query c16][64 f + 4 (4 g + r) + c]
 #pragma unroll
-    for (int i = 0; i < kPer; ++i)
-      op[4 * i + sub] = make_float4(ov[i].x * inv, ov[i].y * inv, ov[i].z * inv, ov[i].w * inv);
-    if (sub == 0 && d.lse) d.lse[(tok0 + qi) * H + h] = (m + log2f(l)) * kLn2;
+  for (int f = 0; f < kF; ++f)
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      po[wave][c16][16 * f + 4 * g + r] = make_float4(ov[4 * f][r], ov[4 * f + 1][r], ov[4 * f + 2][r], ov[4 * f + 3][r]);
+  if (g == 0) {
+    pm[wave][c16] = m;
+    pl[wave][c16] = l;
+  }
+  __syncthreads();
+  for (int e = tid; e < kF32Rows * (D / 4); e += 64 * kWv) {
+    const int row = e / (D / 4), c4 = e % (D / 4);
+    if (q0 + row >= T) break;
+    float mx = pm[0][row];
+#pragma unroll
+    for (int w = 1; w < kWv; ++w) mx = fmaxf(mx, pm[w][row]);
+    float lt = 0.f;
+    float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int w = 0; w < kWv; ++w) {
+      const float a = __builtin_amdgcn_exp2f(pm[w][row] - mx);
+      const float4 x = po[w][row][c4];
+      lt = fmaf(a, pl[w][row], lt);
+      o.x = fmaf(a, x.x, o.x);
+      o.y = fmaf(a, x.y, o.y);
+      o.z = fmaf(a, x.z, o.z);
+      o.w = fmaf(a, x.w, o.w);
+    }
+    const float inv = 1.f / lt;
+    const int64_t orow = (tok0 + q0 + row) * H + h;
+    reinterpret_cast<float4*>(d.o)[orow * (D / 4) + c4] = make_float4(o.x * inv, o.y * inv, o.z * inv, o.w * inv);
+    if (c4 == 0 && d.lse) d.lse[orow] = (mx + log2f(lt)) * kLn2;
   }
 }
 
-// Query tile rows of a launch: 32 per computing wave (bf16), 64 (f32).
+// Query tile rows of a launch: 32 per computing wave (bf16), kF32Rows (f32).
 int attn_rows_per_tile(const focus_attn_desc* d) {
-  return d->dtype == FOCUS_BF16 ? 32 * (d->mask == FOCUS_MASK_KMER_LOCAL ? kBf16WavesKL : kBf16Waves) : 64;
+  return d->dtype == FOCUS_BF16 ? 32 * (d->mask == FOCUS_MASK_KMER_LOCAL ? kBf16WavesKL : kBf16Waves) : kF32Rows;
 }
 
 // Key splits of a C(t) bf16 launch (1 = none): as many as still fit the
@@ -2080,7 +2214,7 @@ extern "C" focus_status focus_window_attn(const focus_attn_desc* d, focus_stream
   const bool kl = d->mask == FOCUS_MASK_KMER_LOCAL;
   const int waves = kl ? kBf16WavesKL : kBf16Waves;
   const int bq = attn_rows_per_tile(d);
-  const int threads = d->dtype == FOCUS_BF16 ? 64 * waves : 256;
+  const int threads = 64 * (d->dtype == FOCUS_BF16 ? waves : kF32Waves);
   const int64_t qt = focus::ceil_div(t.max_window_tokens, bq);
   // Key split when the workspace allows it (else one workgroup per item).
   Split sp = kNoSplit;
@@ -2093,15 +2227,18 @@ extern "C" focus_status focus_window_attn(const focus_attn_desc* d, focus_stream
     sp.po = reinterpret_cast<float*>(d->workspace);
     sp.pml = sp.po + (int64_t)n_split * nwl * sp.rows * d->n_heads * d->head_dim;
   }
-  const int64_t blocks = focus::ceil_div(n_pairs, focus::kXcds) * focus::kXcds * qt * sp.n;
-  if (blocks * threads >= ((int64_t)1 << 32) || qt > INT32_MAX) return FOCUS_E_SHAPE;
+  const int64_t n_pairs8 = focus::ceil_div(n_pairs, focus::kXcds) * focus::kXcds, blocks = n_pairs8 * qt * sp.n;
+  // (f32: the limit counts 64-row tiles; the grid of its smaller ones has a second dimension)
+  const int64_t lim = d->dtype == FOCUS_F32 ? n_pairs8 * focus::ceil_div(t.max_window_tokens, 64) : blocks;
+  if (lim * threads >= ((int64_t)1 << 32) || qt > INT32_MAX) return FOCUS_E_SHAPE;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  const dim3 grid((uint32_t)blocks), block(threads);
-#define FOCUS_ATTN_LAUNCH(KERNEL) hipLaunchKernelGGL(KERNEL, grid, block, 0, s, *d, sc, n_pairs, (int)qt, SumQ{})
+  dim3 grid((uint32_t)blocks), block(threads);
+  if (d->dtype == FOCUS_F32 && blocks >= (1 << 20))
+    grid = dim3(1 << 20, (uint32_t)focus::ceil_div(blocks, 1 << 20));
 #define FOCUS_CT_LAUNCH(KERNEL) hipLaunchKernelGGL(KERNEL, grid, block, 0, s, *d, sc, n_pairs, (int)qt, sp)
 // k-mer-local bf16: one workgroup per (window, head), looping over its query tiles.
 #define FOCUS_KL_LAUNCH(KERNEL, W) hipLaunchKernelGGL(KERNEL, dim3((uint32_t)n_pairs), dim3(64 * (W)), 0, s, *d, sc, n_pairs)
-#define FOCUS_F32_LAUNCH(KERNEL) hipLaunchKernelGGL(KERNEL, grid, block, 0, s, *d, sc, n_pairs, (int)qt, SumQ{})
+#define FOCUS_F32_LAUNCH(KERNEL) hipLaunchKernelGGL(KERNEL, grid, block, 0, s, *d, sc, n_pairs, (int)qt)
   if (d->dtype == FOCUS_BF16) {
     if (d->head_dim == 128) {
       if (kl) FOCUS_KL_LAUNCH((attn_kl<128, kKlWaves128, kKlStages128>), kKlWaves128); else FOCUS_CT_LAUNCH((attn_ct<128>));
@@ -2124,7 +2261,6 @@ extern "C" focus_status focus_window_attn(const focus_attn_desc* d, focus_stream
       if (kl) FOCUS_F32_LAUNCH((attn_f32<64, true>)); else FOCUS_F32_LAUNCH((attn_f32<64, false>));
     }
   }
-#undef FOCUS_ATTN_LAUNCH
 #undef FOCUS_CT_LAUNCH
 #undef FOCUS_F32_LAUNCH
   return focus::launch_status();

@@ -364,3 +364,40 @@ def test_dense_32kb_sampled_rows():
                       p.lse[rows][:, h].cpu().numpy().astype(np.float64), lse_ref)
     del p
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("mask", [F.FOCUS_MASK_CT, F.FOCUS_MASK_KMER_LOCAL])
+def test_f32_infinite_value_stays_with_the_rows_that_see_it(D, mask):
+    """An infinity in V reaches the rows whose visible set holds its key and no
+    other (probability 0 times it would be NaN); the rest is bit-identical."""
+    announce(f"attn f32 infinite V D={D} mask={mask}")
+    seq, W = [333], 333
+    km = np.array([20], np.int32)
+    p = Prefill(seq, W, km, 2, 1, D, "f32", seed=63, run=False)
+    ref = build_layout(seq, W, km)
+    T, t = int(ref["win_ntok"][0]), 200
+    p.o, p.lse = p.attn(mask=mask)
+    p.v[t, 0, D // 2] = float("inf")
+    o, lse = p.attn(mask=mask)
+    vis = A.window_visibility(T, 0) if mask == F.FOCUS_MASK_CT else A.kmer_local_window_visibility(ref, 0)
+    sees = torch.as_tensor(np.asarray(vis)[:, t], device=DEV)
+    want = p.o.clone()
+    want[sees, :, D // 2] = float("inf")
+    assert 0 < int(sees.sum()) < T
+    assert torch.equal(lse, p.lse) and torch.equal(torch.isinf(o), torch.isinf(want))
+    ok = ~torch.isinf(want)
+    # rows in a block with the infinity add its 16 or 32 keys (p v <= 5 each,
+    # rounded to 2^-24 of it) in another order: 32 * 5 * 2^-24 * 2 < 2e-5
+    assert (o[ok] - want[ok]).abs().max().item() <= 2e-5
+
+
+@pytest.mark.parametrize("L,W,kmer,D", [(16, 16, 0, 64), (17, 17, 0, 128), (129, 64, 63, 64), (1, 1, 1, 128), (531, 33, 4, 64)])
+def test_f32_tile_edges(L, W, kmer, D):
+    """float32 windows on and around the 16-row query tile and the key blocks
+    (fewer blocks than waves among them)."""
+    announce(f"attn f32 tile edges L={L} W={W} k={kmer} D={D}")
+    km = np.full(-(-L // W), kmer, np.int32)
+    ref = build_layout([L], W, km)
+    p = Prefill([L], W, km, 3, 1, D, "f32", seed=64)
+    compare_windows(ref, p, range(ref["n_windows"]), [0, 1, 2], "f32 tile edges")
