@@ -14,15 +14,14 @@
 // then only the window tiles that hold the block's k-mers; a two-sided mask
 // keeps each row's own k-mer.
 //
-// bf16 path under C(t) (the hot one, attn_ct): one workgroup = 8 waves x 32
-// query rows of one (window, head), two waves per SIMD; keys arrive in 64-key
-// tiles copied global -> LDS directly through four LDS stages, and each wave
-// runs a one-sub-tile (32 keys) software pipeline:
+// bf16 path under C(t) (the hot one, attn_ct): one workgroup = 4 waves x two
+// blocks of 32 query rows of one (window, head), one wave per SIMD; keys arrive in
+// 64-key tiles copied global -> LDS directly through four LDS stages, and each
+// wave runs a software pipeline over 32-key sub-tiles, one block's MFMAs beside
+// the other's softmax:
 //   S^T = K Q^T   v_mfma_f32_32x32x16_bf16: each lane ends up holding one
 //                 query's scores for 16 keys of a 32-key block, so the row
 //                 max / row sum are lane-local plus one exchange with lane^32;
-//                 the next sub-tile's scores are issued on the MFMA pipe while
-//                 the VALU does this sub-tile's softmax;
 //   softmax       exp2 domain, running reference with lazy rescaling: the row
 //                 maximum is taken and the output accumulator rescaled only when
 //                 a lane's 16 probabilities sum to more than 2^12, which is exact
@@ -55,6 +54,8 @@
 
 #include <math.h>
 
+#include <type_traits>
+
 namespace {
 
 using focus::bf16x4;
@@ -72,10 +73,10 @@ constexpr float kLazySum = 4096.f;  // ... or when a lane's 16 probabilities sum
 typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
 typedef __attribute__((address_space(3))) void lds_void;
 
-// Waves per workgroup of the bf16 kernels (each wave owns 32 query rows):
-// eight under C(t), where a workgroup streams thousands of keys; four under the
-// k-mer-local mask (attn_kl), where a query tile visits a handful of key tiles.
-constexpr int kBf16Waves = 8;
+// The bf16 kernels' workgroups: under C(t) four waves of 64 query rows (attn_ct);
+// under the k-mer-local mask four waves of 32 (attn_kl), whose query tiles visit a
+// handful of key tiles.
+constexpr int kCtRows = 256, kCtWaves = 4;
 constexpr int kBf16WavesKL = 4;
 // attn_kl at head_dim 128: waves per workgroup and LDS stages (8 waves and 8
 // stages, one workgroup per CU: 8.41 vs 7.86 ms at 1 Mb)
@@ -97,45 +98,19 @@ struct Item {
 // the workgroups that run together on an XCD then stream the same cache rows
 // of one head at about the same time, so each row is fetched into its L2 once
 // for all of them.  Otherwise pair p = list_idx * H + h goes to XCD p % 8, in
-// increasing p.  The QT query tiles of a pair go last-first (under the causal
-// window mask the last tile sees the most keys, and starting the longest
-// workgroups first shortens the tail of a launch).
-//
-// Two orders of an XCD's blocks (H a multiple of 8):
-// * ROUNDS = false: a pair's query tiles are consecutive blocks (they share
-//   the window's K/V through the XCD's L2 while they run together);
-// * ROUNDS = true: kRound consecutive blocks (one per compute unit of the XCD)
-//   are one query tile of kRound pairs, the next kRound the next query tile of
-//   the same pairs.  The hardware hands an XCD's blocks to its compute units in
-//   a fixed rotation, so with the first order each compute unit always gets
-//   the same query tile, and the ones with short tiles wait every round for
-//   the ones with long tiles (per-workgroup timestamps: ~12 us idle per
-//   workgroup at 1 Mb).  With one tile per round the workgroups of a round
-//   last about equally long.  It pays where the arithmetic dominates (the C(t)
-//   attention: 1 Mb 88.6 -> 86.7 ms, 100 kb 2.70 -> 2.58 ms); the HBM-bound
-//   k-mer-local launch loses more from the scattered K/V reuse (9.6 -> 10.5 ms)
-//   and keeps the first order.
-constexpr int64_t kRound = 32;  // compute units per XCD on MI355X (256 / 8)
-template <bool ROUNDS = false>
+// increasing p.  The QT query tiles of a pair are consecutive blocks, last-first
+// (under the causal window mask the last tile sees the most keys, and starting
+// the longest workgroups first shortens the tail of a launch).
 __device__ inline Item map_block(int64_t bid, int64_t n_pairs, int H, int QT) {
   const int x = (int)(bid % focus::kXcds);
   const int64_t s = bid / focus::kXcds;
   Item it;
   it.qt = QT - 1 - (int)(s % QT);
-  int64_t j = s / QT;  // this XCD's j-th pair
+  const int64_t j = s / QT;  // this XCD's j-th pair
   if (H % focus::kXcds == 0) {
-    bool in_range = true;
-    if (ROUNDS) {
-      const int64_t npx = n_pairs / focus::kXcds;  // pairs of this XCD
-      const int64_t c = s / (kRound * QT), r = s % (kRound * QT);
-      const int64_t m = min(kRound, npx - c * kRound);  // pairs in this group of rounds
-      in_range = m > 0 && r < m * QT;
-      j = c * kRound + (in_range ? r % m : 0);
-      it.qt = QT - 1 - (in_range ? (int)(r / m) : 0);
-    }
     const int64_t nwl = n_pairs / H;  // listed windows
     const int64_t hl = nwl > 0 ? j / nwl : 0;
-    it.valid = in_range && nwl > 0 && hl < H / focus::kXcds;
+    it.valid = nwl > 0 && hl < H / focus::kXcds;
     it.list_idx = nwl > 0 ? j % nwl : 0;
     it.h = (int)(hl * focus::kXcds + x);
   } else {
@@ -146,6 +121,15 @@ __device__ inline Item map_block(int64_t bid, int64_t n_pairs, int H, int QT) {
   }
   return it;
 }
+
+// attn_ct's order where H is a multiple of 8: kRound consecutive blocks of an XCD
+// (one per compute unit of it) are one query tile of kRound pairs, the next kRound
+// the next query tile of the same pairs.  The hardware hands an XCD's blocks to
+// its compute units in a fixed rotation, so with map_block's order each compute
+// unit always gets the same query tile, and the ones with short tiles wait every
+// round for the ones with long tiles (~12 us idle per workgroup at 1 Mb; 88.6 ->
+// 86.7 ms there, 2.70 -> 2.58 at 100 kb).
+constexpr int64_t kRound = 32;  // compute units per XCD on MI355X (256 / 8)
 
 __device__ inline int64_t listed_window(const focus_attn_desc& d, int64_t li) {
   return d.win_ids ? (int64_t)d.win_ids[li] : d.totals.n_windows - 1 - li;
@@ -1004,24 +988,40 @@ __device__ __forceinline__ float row_max(const f32x16& s) {
 
 // ------------------------------------------- bf16 MFMA, C(t), pipelined waves
 
-// The C(t) window attention: one workgroup = 8 waves x 32 query rows of one
-// (window, head), two waves per SIMD (up to 256 registers each).  Keys arrive
-// in 64-key tiles through four LDS stages (copies issued by every wave, three
-// tiles ahead, spread over the step); each wave walks the keys in 32-key
-// sub-tiles with a one-sub-tile software pipeline:
-//   V^T operands of sub-tile j are read from LDS;
-//   S_{j+1} = K_{j+1} Q^T is issued on the MFMA pipe (its K operands were read
-//     one sub-tile earlier), and runs while the VALU does the softmax of S_j;
-//   the K operands of sub-tile j + 2 are read;
-//   O^T += V_j^T P_j^T.
-// So every LDS operand is read about one sub-tile before its MFMA, and the
-// exponentials of one sub-tile overlap the score MFMAs of the next.  A
+// The C(t) window attention: one workgroup = 256 query rows of one (window,
+// head) = 4 waves x two blocks of 32 rows, one wave per SIMD.  Keys arrive in
+// 64-key tiles through four LDS stages (copies issued by every wave, three
+// tiles ahead); each wave walks the keys in 32-key sub-tiles, and both its
+// query blocks use a sub-tile's K and V operands from the same registers, so an
+// operand is read from LDS once for two MFMAs.  A sub-tile j takes two phases:
+//   A   S_{j+1} = K_{j+1} Q^T and O^T += V_j^T P_j^T of block 0 on the MFMA pipe,
+//       while the VALU does the softmax of block 1's S_j;
+//   B   the same products of block 1, while the VALU does the softmax of block
+//       0's S_{j+1}; each K or V operand is replaced by the next sub-tile's as
+//       soon as its MFMA has been issued.
+// So the softmax always works on scores that are complete, every operand is read
+// half a phase or more before its MFMA, and with one wave per SIMD the order of
+// the instructions is the whole schedule: the phases are written out MFMA by
+// MFMA with the vector instructions, reads and copies dealt between them.  A
 // barrier closes every 64-key step; at its end each wave waits only for the
 // copies of the tile the next step starts reading.
+//
+// What bounds it: the chip's power limit and, with one wave per SIMD, issue slots
+// (a phase of 16 MFMAs has 102 instructions, 61 of them vector; the MFMA pipe is
+// busy 0.69 of the cycles at 32 kb dense).  Against eight waves of 32 rows with
+// two waves per SIMD, which read every operand for one MFMA: 1 Mb 82.7 -> 78.3
+// ms, 32 kb dense 7.20 -> 6.66, 100 kb 2.14 -> 2.10, the ragged batch 12.5 -> 12.1,
+// 100 kb at head_dim 64 1.30 -> 1.15, windows of 512 5.5 -> 4.8, one window per
+// call 172 -> 162 us (one box).  A workgroup of 18 tiles takes 1.85 us a clean
+// step, 2.08 a masked one, and about 9 us before, between and after.
+// A persistent form (one workgroup per compute unit over many items, the next
+// item's first tiles and Q on their way during the last steps) was slower: 1 Mb
+// 81.8 ms, 100 kb 2.25; so were branches around dead sub-tiles in the masked steps
+// (the accumulators of the two sides met in different registers: 500 spills).
 template <int D>
 struct CtCfg {
-  static constexpr int kWaves = 8;
-  static constexpr int kBQ = 32 * kWaves;                // query rows per block
+  static constexpr int kWaves = 4;
+  static constexpr int kBQ = 64 * kWaves;                // query rows per block
   static constexpr int kBK = 64;                         // keys per LDS tile
   static constexpr int kRB = D * 2;                      // bytes per row
   static constexpr int kTile = kBK * kRB;                // bytes per tile per tensor
@@ -1031,67 +1031,131 @@ struct CtCfg {
   static constexpr int kRPK = 1024 / kRB;                // tile rows per 1 KB wave copy
   static constexpr int kDma = kTile / 1024 / kWaves;     // wave copies per tile, tensor and wave
   static constexpr int kPerStep = 2 * kDma;              // copies a wave issues per step
+  static constexpr int kMfma = kKsteps + 2 * kDtiles;    // MFMAs of a phase
 };
 
+// Exponentials done after c + 1 of a phase's n MFMAs: all 16 by the last but two,
+// so that the sum's test is ready at the end of the phase.
+__device__ constexpr int ct_exps(int c, int n) {
+  const int e = c < 0 ? 0 : ((c + 1) * 16 + n - 3) / (n - 2);
+  return e < 16 ? e : 16;
+}
+
+// A value that every lane has, in scalar registers.
+__device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ __forceinline__ int64_t uniform(int64_t x) {
+  return (int64_t)((uint64_t)(uint32_t)uniform((int)(x >> 32)) << 32 | (uint32_t)uniform((int)x));
+}
+
+// f(integral_constant) for 0 .. N - 1
+template <int N, class F>
+__device__ __forceinline__ void each(F f) {
+  if constexpr (N > 0) {
+    each<N - 1>(f);
+    f(std::integral_constant<int, N - 1>());
+  }
+}
+
+// 16 bytes per lane from base + off to LDS byte lds + IMM + 16 lane (the
+// instruction adds its immediate to both addresses, so base is IMM bytes early).
+template <int IMM>
+__device__ __forceinline__ void copy_to_lds(const char* base, uint32_t off, uint32_t lds) {
+  asm volatile(
+      "s_nop 0\n\t"
+      "global_load_lds_dwordx4 %0, %1 offset:%3"
+      :
+      : "v"(off), "s"(base), "{m0}"(lds), "n"(IMM)
+      : "memory");
+}
+
 template <int D>
-__global__ __launch_bounds__(512, 2) void attn_ct(
+__global__ __launch_bounds__(256, 1) void attn_ct(
     focus_attn_desc d, float sc, int64_t n_pairs, int QT, Split sp) {
   using C = CtCfg<D>;
   static_assert(C::kDma >= 1 && C::kTile % (1024 * C::kWaves) == 0, "tile must split into 1 KB wave loads");
-  // Four K and four V stages as separate arrays, every reference static (the
-  // step loop is unrolled four times): the compiler then tells the buffer a
-  // read uses from the ones being filled.
-  __shared__ __attribute__((aligned(1024))) char kb0[C::kTile], kb1[C::kTile], kb2[C::kTile], kb3[C::kTile];
-  __shared__ __attribute__((aligned(1024))) char vb0[C::kTile], vb1[C::kTile], vb2[C::kTile], vb3[C::kTile];
+  // K stages, then V stages
+  __shared__ __attribute__((aligned(1024))) char lds[8 * C::kTile];
 
+  // Block -> (listed window, head, query tile, key split): rounds (kRound) or
+  // map_block's other order, in 32-bit arithmetic (the host bounds the blocks).
   const int tid = threadIdx.x;
-  int64_t bid = blockIdx.x;
-  int split = 0;
+  // (the arguments of the chain of loads ahead, fetched together)
+  asm volatile("" ::"s"(n_pairs), "s"(QT), "s"(sp.n), "s"(d.win_ids), "s"(d.win_seq), "s"(d.win_ntok),
+               "s"(d.win_cache_off), "s"(d.win_tok_off), "s"(d.totals.n_windows), "s"(d.n_heads), "s"(d.n_kv_heads),
+               "s"(d.qkv_tok_base), "s"(d.qkv_rows), "s"(d.cache_cap), "s"(d.batch));
+  const uint32_t np = (uint32_t)n_pairs, qt_n = (uint32_t)QT, uH = (uint32_t)d.n_heads;
+  const uint32_t x = blockIdx.x % focus::kXcds;
+  uint32_t r = blockIdx.x / focus::kXcds, split = 0;
   if (sp.n > 1) {
-    const int64_t r = bid / focus::kXcds;
-    split = (int)(r % sp.n);
-    bid = (r / sp.n) * focus::kXcds + bid % focus::kXcds;
+    split = r % (uint32_t)sp.n;
+    r /= (uint32_t)sp.n;
   }
-  const Item it = map_block<true>(bid, n_pairs, d.n_heads, QT);
-  if (!it.valid) return;
-  const int64_t gw = listed_window(d, it.list_idx);
+  uint32_t li, uh, qt;
+  if (uH % focus::kXcds == 0) {
+    constexpr uint32_t kR = (uint32_t)kRound;
+    const uint32_t c = r / (kR * qt_n), left = np / focus::kXcds - c * kR, m = left < kR ? left : kR;
+    r -= c * kR * qt_n;
+    qt = r / m;  // (m > 0: the grid has no blocks past the last pair)
+    const uint32_t j = c * kR + r - qt * m, nwl = np / uH;
+    uh = j / nwl;
+    li = j - uh * nwl;
+    uh = uh * focus::kXcds + x;
+  } else {
+    const uint32_t j = r / qt_n, p = j * focus::kXcds + x;
+    if (p >= np) return;
+    qt = r - j * qt_n;
+    li = p / uH;
+    uh = p - li * uH;
+  }
+  qt = qt_n - 1 - qt;
+  const int64_t gw = listed_window(d, li);
   if (gw < 0 || gw >= d.totals.n_windows) {
-    if (tid == 0 && it.qt == 0) focus::raise_err(d.err, FOCUS_ERR_BOUNDS);
+    if (tid == 0 && qt == 0) focus::raise_err(d.err, FOCUS_ERR_BOUNDS);
     return;
   }
-  const int T = d.win_ntok[gw];
-  const int q0 = it.qt * C::kBQ;
+  // (the four loads together: left alone, each is issued behind a test of the last)
+  int Cw = d.win_cache_off[gw], b = d.win_seq[gw], T = d.win_ntok[gw];
+  int64_t tok0 = d.win_tok_off[gw];
+  asm volatile("" : "+v"(Cw), "+v"(b), "+v"(T), "+v"(tok0));
+  Cw = uniform(Cw);
+  b = uniform(b);
+  T = uniform(T);
+  tok0 = uniform(tok0) - d.qkv_tok_base;
+  const int q0 = (int)qt * C::kBQ;
   if (q0 >= T) return;
-  const int Cw = d.win_cache_off[gw];
-  const int b = d.win_seq[gw];
-  const int64_t tok0 = d.win_tok_off[gw] - d.qkv_tok_base;
   if (b < 0 || b >= d.batch || Cw < 0 || Cw > d.cache_cap || tok0 < 0 || tok0 + T > d.qkv_rows) {
     if (tid == 0) focus::raise_err(d.err, FOCUS_ERR_BOUNDS);
     return;
   }
-  const int H = d.n_heads, Hkv = d.n_kv_heads, h = it.h;
-  const int hk = h / (H / Hkv);
+  const int H = d.n_heads, Hkv = d.n_kv_heads, h = (int)uh;
+  const int hk = (int)(uh / (uH / (uint32_t)Hkv));
   const int nwk = min(T, q0 + C::kBQ);  // window keys any query of this block sees
   // keys: nct tiles of cache rows [0, Cw), then nwt tiles of window rows [0, nwk)
   const int nct = (Cw + C::kBK - 1) / C::kBK;
   const int nwt = (nwk + C::kBK - 1) / C::kBK;
-  const int tb = (int)((int64_t)split * (nct + nwt) / sp.n);
-  const int ntiles = (int)((int64_t)(split + 1) * (nct + nwt) / sp.n) - tb;
+  int tb = 0, ntiles = nct + nwt;
+  if (sp.n > 1) {
+    tb = (int)((int64_t)split * (nct + nwt) / sp.n);
+    ntiles = (int)((int64_t)(split + 1) * (nct + nwt) / sp.n) - tb;
+  }
 
   // (the wave index through readfirstlane: the compiler then keeps everything
   // derived from it in scalar registers and branches on it with scalar tests)
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l32 = lane & 31, g = lane >> 5;
-  const int qi = q0 + wave * 32 + l32;
-  const int wq_lo = q0 + wave * 32, wq_hi = min(wq_lo + 31, T - 1);
-  const bool wave_live = wq_lo < T;
+  // A wave's query blocks: rows q0 + 32 (7 - wave) and q0 + 32 wave, so that
+  // the longer of every wave's two is well above the first diagonal tile (see
+  // the clean steps below).
+  const int wq[2] = {q0 + 32 * (2 * C::kWaves - 1 - wave), q0 + 32 * wave};
+  const int qi[2] = {wq[0] + l32, wq[1] + l32};
 
   // Q^T as the B operand: lane holds query l32, head_dim [16 s + 8 g, +8).
-  bf16x8 qf[C::kKsteps];
-  {
-    const bf16x8* qp = reinterpret_cast<const bf16x8*>(reinterpret_cast<const __bf16*>(d.q) +
-                                                       ((tok0 + min(qi, T - 1)) * H + h) * D);
+  bf16x8 qf[2][C::kKsteps];
 #pragma unroll
-    for (int s = 0; s < C::kKsteps; ++s) qf[s] = qp[2 * s + g];
+  for (int i = 0; i < 2; ++i) {
+    const bf16x8* qp = reinterpret_cast<const bf16x8*>(reinterpret_cast<const __bf16*>(d.q) +
+                                                       ((tok0 + min(qi[i], T - 1)) * H + h) * D);
+#pragma unroll
+    for (int s = 0; s < C::kKsteps; ++s) qf[i][s] = qp[2 * s + g];
   }
 
   // Copies: wave copy i of this wave fills tile rows (wave kDma + i) kRPK +
@@ -1100,15 +1164,15 @@ __global__ __launch_bounds__(512, 2) void attn_ct(
   // V: 64-byte granule x of row r at x ^ f(r)).  The last tile of a phase
   // clamps its rows to the last valid one (the extra rows are masked).
   const uint32_t row_bytes = (uint32_t)(Hkv * D * 2);
-  uint32_t rowb[C::kDma], kchunk[C::kDma], vchunk[C::kDma];
+  constexpr int kLast = (C::kDma - 1) * 1024;  // immediate of the last copy of a tensor
+  uint32_t koff[C::kDma], voff[C::kDma];
 #pragma unroll
   for (int i = 0; i < C::kDma; ++i) {
     const int r = (wave * C::kDma + i) * C::kRPK + lane / C::kCh16;
     const int p = lane % C::kCh16;
     const int f = D == 128 ? (r & 3) : ((r >> 1) & 1);
-    rowb[i] = (uint32_t)r * row_bytes;
-    kchunk[i] = (uint32_t)((p ^ (r % C::kCh16)) * 16);
-    vchunk[i] = (uint32_t)((((p >> 2) ^ f) * 4 + (p & 3)) * 16);
+    koff[i] = (uint32_t)r * row_bytes + (uint32_t)((p ^ (r % C::kCh16)) * 16) + kLast - i * 1024;
+    voff[i] = (uint32_t)r * row_bytes + (uint32_t)((((p >> 2) ^ f) * 4 + (p & 3)) * 16) + kLast - i * 1024;
   }
   const char* kwin = reinterpret_cast<const char*>(reinterpret_cast<const __bf16*>(d.k) + (tok0 * Hkv + hk) * D);
   const char* vwin = reinterpret_cast<const char*>(reinterpret_cast<const __bf16*>(d.v) + (tok0 * Hkv + hk) * D);
@@ -1120,188 +1184,247 @@ __global__ __launch_bounds__(512, 2) void attn_ct(
   // pad = 64 nct - C_w rows before cache row 0, so the one partial cache tile
   // is tile 0 (its first pad rows are not keys) and every later tile up to
   // the block's diagonal is full and unmasked.  Copy sources: tile tg starts
-  // at (tg < nct ? cache - pad rows : window - nct tiles) + tg tiles.  Wave
-  // copy i of a tile (K and V) into (kbuf, vbuf); a partial tile clamps its
-  // rows into [lo, last], the valid ones.
+  // at (tg < nct ? cache - pad rows : window - nct tiles) + tg tiles; a partial
+  // tile clamps its rows into [lo, last], the valid ones.
   const int pad = nct * C::kBK - Cw;
   const int64_t tstride = (int64_t)C::kBK * row_bytes;
-  const char* kcache_b = kcache - (int64_t)pad * row_bytes;
-  const char* vcache_b = vcache - (int64_t)pad * row_bytes;
-  const char* kwin_b = kwin - nct * tstride;
-  const char* vwin_b = vwin - nct * tstride;
+  const char* kcache_b = kcache - (int64_t)pad * row_bytes - kLast;
+  const char* vcache_b = vcache - (int64_t)pad * row_bytes - kLast;
+  const char* kwin_b = kwin - nct * tstride - kLast;
+  const char* vwin_b = vwin - nct * tstride - kLast;
   const int wfull = nct + nwk / C::kBK;        // window tiles in [nct, wfull) are full
   struct Src {
     const char* k;
     const char* v;
     uint32_t lo, last;  // byte offsets of the tile's first and last valid rows
-    bool full;
   };
   auto tile_src = [&](int u) __attribute__((always_inline)) {
     const int tg = tb + u;
     const bool in_cache = tg < nct;
     Src r;
-    r.k = (in_cache ? kcache_b : kwin_b) + tg * tstride;
-    r.v = (in_cache ? vcache_b : vwin_b) + tg * tstride;
-    r.full = in_cache ? (tg > 0 || pad == 0) : tg < wfull;
+    r.k = reinterpret_cast<const char*>(uniform(reinterpret_cast<int64_t>(in_cache ? kcache_b : kwin_b) + tg * tstride));
+    r.v = reinterpret_cast<const char*>(uniform(reinterpret_cast<int64_t>(in_cache ? vcache_b : vwin_b) + tg * tstride));
     r.lo = (uint32_t)(in_cache && tg == 0 ? pad : 0) * row_bytes;
     r.last = (uint32_t)(in_cache ? C::kBK - 1 : min(C::kBK, nwk - (tg - nct) * C::kBK) - 1) * row_bytes;
     return r;
   };
-  auto issue = [&](const Src& sr, char* kbuf, char* vbuf, int i, bool clamp) __attribute__((always_inline)) {
-    const uint32_t rb = clamp ? min(max(rowb[i], sr.lo), sr.last) : rowb[i];
-    const char* ks = sr.k + (rb + kchunk[i]);
-    const char* vs = sr.v + (rb + vchunk[i]);
-    char* kl = kbuf + (wave * C::kDma + i) * 1024;
-    char* vl = vbuf + (wave * C::kDma + i) * 1024;
-    __builtin_amdgcn_global_load_lds(ks, (lds_void*)kl, 16, 0, 0);
-    __builtin_amdgcn_global_load_lds(vs, (lds_void*)vl, 16, 0, 0);
+  const uint32_t lds0 = lds_addr(lds), ldsw = lds0 + (uint32_t)(wave * C::kDma) * 1024;
+  // copy c of a tile into stage st: K for c < kDma, then V
+  auto issue = [&](const Src& sr, int st, auto c_c, bool clamp) __attribute__((always_inline)) {
+    constexpr int c = decltype(c_c)::value, i = c % C::kDma;
+    uint32_t off = c < C::kDma ? koff[i] : voff[i];
+    if (clamp) {
+      // row r in [lo, last] instead (the rest of the offset stays)
+      const uint32_t rb = (uint32_t)((wave * C::kDma + i) * C::kRPK + lane / C::kCh16) * row_bytes;
+      off += min(max(rb, sr.lo), sr.last) - rb;
+    }
+    copy_to_lds<i * 1024>(c < C::kDma ? sr.k : sr.v, off, ldsw + ((c < C::kDma ? 0 : 4) + st) * C::kTile);
+  };
+  auto issue_tile = [&](const Src& sr, int st) __attribute__((always_inline)) {
+    each<2 * C::kDma>([&](auto c) __attribute__((always_inline)) { issue(sr, st, c, true); });
   };
 
-  // Sub-tile j (32 keys) = half j & 1 of local tile j >> 1, i.e. global
-  // sub-tile J = 2 tb + j: stream rows [32 J, 32 J + 32), cache row
-  // 32 J + r - pad while J < 2 nct, then window row 32 (J - 2 nct) + r.  This
-  // wave computes sub-tiles j < jlive (the window rows past its last query
-  // are skipped).  Masks: the rows of tile 0 below pad, and the window rows
-  // past the query (from the wave's first diagonal sub-tile, wmask, on).
+  // Sub-tile j of the local tiles is stream rows [32 J, 32 J + 32), J = 2 tb + j:
+  // cache row 32 J + r - pad while J < 2 nct, then window row 32 (J - 2 nct) + r.
   const int J0 = 2 * tb;
-  const int jlive = wave_live ? min(2 * (tb + ntiles), 2 * nct + (wq_hi >> 5) + 1) - J0 : 0;
-  const int wmask = 2 * nct + (wq_lo >> 5);
-  auto need_mask = [&](int J) { return 32 * J < pad || J >= wmask; };
 
-  // LDS operand offsets (lane parts; buffers and sub-tile rows are immediates).
+  // LDS operand addresses (lane parts; stages and sub-tile rows are immediates).
   // K row 32 half + l32, chunk 2 s + g sits at chunk (2 s + g) ^ (l32 mod kCh16).
-  int kofs[C::kKsteps];
+  uint32_t kofs[C::kKsteps];
   {
     const int kx = g ^ (l32 & (C::kCh16 - 1));
 #pragma unroll
-    for (int s = 0; s < C::kKsteps; ++s) kofs[s] = l32 * C::kRB + (((2 * s) ^ kx) << 4);
+    for (int s = 0; s < C::kKsteps; ++s) kofs[s] = lds0 + l32 * C::kRB + (((2 * s) ^ kx) << 4);
   }
   // V^T operand: lane = 16 grp + 4 ri + bq reads row 4 (grp / 2) + ri (+ 16 m,
   // + 8 for the upper half) of the sub-tile, bytes 64 dt + 32 (grp & 1) + 8 bq,
   // whose 64-byte granule sits at dt ^ f (f = ri, or ri / 2 for D = 64).
-  int vofs[C::kDtiles];
+  uint32_t vofs[C::kDtiles];
   {
     const int grp = lane >> 4, ri = (lane >> 2) & 3, bq = lane & 3;
     const int f = D == 128 ? ri : (ri >> 1) & 1;
 #pragma unroll
     for (int dt = 0; dt < C::kDtiles; ++dt)
-      vofs[dt] = (4 * (grp >> 1) + ri) * C::kRB + 32 * (grp & 1) + 8 * bq + ((dt ^ f) << 6);
+      vofs[dt] = lds0 + 4 * C::kTile + (4 * (grp >> 1) + ri) * C::kRB + 32 * (grp & 1) + 8 * bq + ((dt ^ f) << 6);
   }
-  // Keeps the offsets opaque to loop-invariant code motion, so the compiler
-  // folds buffer and row into the instructions' immediate offsets instead of
-  // holding one address register per (buffer, operand).
-  auto pin_offsets = [&]() __attribute__((always_inline)) {
-#pragma unroll
-    for (int s = 0; s < C::kKsteps; ++s) asm volatile("" : "+v"(kofs[s]));
-#pragma unroll
-    for (int dt = 0; dt < C::kDtiles; ++dt) asm volatile("" : "+v"(vofs[dt]));
+  // kofs follows the tile whose K is read next, vofs the tile whose V is.
+  auto next_stage = [&](uint32_t& adr, int st) __attribute__((always_inline)) {
+    adr += st == 3 ? -3 * C::kTile : C::kTile;
   };
 
-  bf16x8 kop[C::kKsteps];
-  auto read_k = [&](const char* kbuf, int half) __attribute__((always_inline)) {
-#pragma unroll
-    for (int s = 0; s < C::kKsteps; ++s)
-      kop[s] = *reinterpret_cast<const bf16x8*>(kbuf + (kofs[s] + half * 32 * C::kRB));
+  bf16x8 kop[C::kKsteps], vop[2 * C::kDtiles];
+  typedef __attribute__((address_space(3))) bf16x8 lds_bf16x8;
+  auto read_k = [&](int half, int s) __attribute__((always_inline)) {
+    kop[s] = *(const lds_bf16x8*)(uintptr_t)(kofs[s] + half * 32 * C::kRB);
   };
-  f32x16 sacc[2];
-  auto qk = [&](f32x16& acc) __attribute__((always_inline)) {
-#pragma unroll
-    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-#pragma unroll
-    for (int s = 0; s < C::kKsteps; ++s) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kop[s], qf[s], acc, 0, 0, 0);
+  auto read_v = [&](int half, int x) __attribute__((always_inline)) {
+    const uint32_t a = vofs[x % C::kDtiles] + (32 * half + 16 * (x / C::kDtiles)) * C::kRB;
+    const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(uintptr_t)a);
+    const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(uintptr_t)(a + 8 * C::kRB));
+    vop[x] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
   };
 
-  f32x16 oacc[C::kDtiles];
+  f32x16 sacc[2], oacc[2][C::kDtiles];
+  u32x4 pb[2][2];
+  float m_run[2] = {kMinit, kMinit}, l_run[2] = {0.f, 0.f};
 #pragma unroll
-  for (int dt = 0; dt < C::kDtiles; ++dt)
+  for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) oacc[dt][v] = 0.f;
-  float m_run = kMinit, l_run = 0.f;
+    for (int dt = 0; dt < C::kDtiles; ++dt)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) oacc[i][dt][v] = 0.f;
 
-  // One sub-tile iteration (see the header).  half = j & 1 is a constant
-  // after inlining; kc / vc hold tile j >> 1, kn tile (j >> 1) + 1; copies of
-  // tile u + 3 go to (kcp, vcp).
-  auto sub = [&](int j, const int half, const bool fast, const char* vc, const char* kn, char* kcp, char* vcp,
-                 int u, const Src& src) __attribute__((always_inline)) {
-    const bool lj = fast || j < jlive, lj1 = fast || j + 1 < jlive;
-    // A wave keeps at most 15 LDS reads in flight (the counter's range), so
-    // the 16 V^T reads go in two halves around the score MFMAs, and the 8 K
-    // reads follow the softmax's row maximum.  The reads are unconditional (a
-    // dead sub-tile reads a stale but valid buffer), so the compiler's
-    // counter waits stay exact.
-    bf16x8 vop[2 * C::kDtiles];
-    auto read_v = [&](int m) __attribute__((always_inline)) {
+  // The accumulators of O^T are in the AGPRs, which only MFMAs touch in the loop,
+  // and the scores in VGPRs, where the softmax reads them.  The compiler gives
+  // all of a kernel's MFMAs one kind (with AGPRs, 16 of 73 vector instructions a
+  // phase copied scores), so the output products are inline assembly.  Their
+  // hazards are kept here: pb is written at least two instructions before they
+  // read it, and o_ready() stands between them and any other access to oacc.
+  auto mfma_s = [&](int i, int s) __attribute__((always_inline)) {
+    if (s == 0)
 #pragma unroll
-      for (int dt = 0; dt < C::kDtiles; ++dt) {
-        const char* p = vc + (vofs[dt] + (32 * half + 16 * m) * C::kRB);
-        const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)p);
-        const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(p + 8 * C::kRB));
-        vop[m * C::kDtiles + dt] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-      }
-    };
-    read_v(0);
-    // S_{j+1}: its K operands were read one sub-tile earlier
-    if (lj1) qk(sacc[half ^ 1]);
-    read_v(1);
-    if (fast || u + 3 < ntiles) {
+      for (int v = 0; v < 16; ++v) sacc[i][v] = 0.f;
+    sacc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kop[s], qf[i][s], sacc[i], 0, 0, 0);
+  };
+  auto mfma_o = [&](int i, int x) __attribute__((always_inline)) {
+    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0"
+                 : "+a"(oacc[i][x % C::kDtiles])
+                 : "v"(vop[x]), "v"(pb[i][x / C::kDtiles]));
+  };
+  auto o_ready = [&](int i) __attribute__((always_inline)) {
 #pragma unroll
-      for (int i = 0; i < C::kDma; ++i)
-        if ((i & 1) == half) issue(src, kcp, vcp, i, !fast && !src.full);
+    for (int dt = 0; dt < C::kDtiles; ++dt) asm volatile("s_nop 15" : "+a"(oacc[i][dt]));
+  };
+  // Of block i's scores of sub-tile j (32 keys: half j & 1 of the local tile
+  // j >> 1), s[v] is key 8 (v / 4) + 4 g + v % 4.  Masked are the rows of tile 0
+  // before cache row 0 (mode 2 only), the window rows past the query and what
+  // lies past the stream (nothing was copied there).
+  typedef std::integral_constant<int, 0> mask_none;
+  typedef std::integral_constant<int, 1> mask_hi;
+  typedef std::integral_constant<int, 2> mask_lo_hi;
+  struct Mask {
+    int lo, hi;
+  };
+  auto mask_of = [&](int i, int j) __attribute__((always_inline)) {
+    const int J = J0 + j;
+    Mask mk = {-1, 64};
+    if (J < 2 * nct)
+      mk.lo = pad - 32 * J - 4 * g;
+    else
+      mk.hi = qi[i] - 32 * (J - 2 * nct) - 4 * g;
+    if (j >= 2 * ntiles) mk.hi = -1;
+    return mk;
+  };
+  auto score = [&](auto mode, int i, int v, const Mask& mk) __attribute__((always_inline)) {
+    constexpr int M = decltype(mode)::value;
+    const int kk = (v >> 2) * 8 + (v & 3);
+    float x = sacc[i][v];
+    if (M >= 1) x = kk > mk.hi ? -INFINITY : x;
+    if (M == 2) x = kk < mk.lo ? -INFINITY : x;
+    return x;
+  };
+  // The probabilities of block i's scores against its running reference, and
+  // their sum over the lane's 16 keys.
+  auto probs = [&](auto mode, int i, const Mask& mk) __attribute__((always_inline)) {
+    float psum = 0.f;
+#pragma unroll
+    for (int v = 0; v < 16; v += 2) {
+      const float p0 = __builtin_amdgcn_exp2f(fmaf(score(mode, i, v, mk), sc, -m_run[i]));
+      const float p1 = __builtin_amdgcn_exp2f(fmaf(score(mode, i, v + 1, mk), sc, -m_run[i]));
+      psum += p0;
+      psum += p1;
+      pb[i][v >> 3][(v >> 1) & 3] = focus::pack_bf16x2(p0, p1);
     }
-    // K operands of sub-tile j + 2
-    read_k(kn, half);
-    if (lj) {
-      f32x16& s = sacc[half];
-      const int J = J0 + j;
-      if (!fast && need_mask(J)) {
-        // s[v] = score of query qi with sub-tile key 8 (v/4) + 4 g + v%4
-        if (J < 2 * nct) {
-          const int lo_g = pad - 32 * J - 4 * g;  // rows of tile 0 before cache row 0
+    return psum;
+  };
+  // The sum, which the row sum needs anyway, says whether the reference is still
+  // high enough (numerator and denominator use the same one, so any is exact).
+  // If not: the row's maximum, the accumulator rescaled, the probabilities again.
+  auto settle = [&](auto mode, int i, float psum, bool big, const Mask& mk) __attribute__((always_inline)) {
+    if (__builtin_expect(big, 0)) {
+      f32x16 s;
 #pragma unroll
-          for (int v = 0; v < 16; ++v)
-            if ((v >> 2) * 8 + (v & 3) < lo_g) s[v] = -INFINITY;
-        } else {
-          const int lim_g = qi - 32 * (J - 2 * nct) - 4 * g;
+      for (int v = 0; v < 16; ++v) s[v] = score(mode, i, v, mk);
+      const float m_new = fmaxf(m_run[i], row_max(s) * sc);
+      const float alpha = __builtin_amdgcn_exp2f(m_run[i] - m_new);
+      l_run[i] *= alpha;
+      o_ready(i);
 #pragma unroll
-          for (int v = 0; v < 16; ++v)
-            if ((v >> 2) * 8 + (v & 3) > lim_g) s[v] = -INFINITY;
-        }
-      }
-      // The probabilities against the running reference; their sum, which the
-      // row sum needs anyway, says whether the reference is still high enough
-      // (numerator and denominator use the same one, so any is exact).  A row
-      // maximum per sub-tile cost 15 of 75 vector instructions and sat between
-      // the scores and the exponentials: 1 Mb 88.5 -> 87.0 ms, 100 kb 2.28 -> 2.25.
-      bf16x8 pb[2];
-      float psum;
-      auto probs = [&]() __attribute__((always_inline)) {
-        psum = 0.f;
+      for (int dt = 0; dt < C::kDtiles; ++dt)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const float p = __builtin_amdgcn_exp2f(fmaf(s[v], sc, -m_run));
-          psum += p;
-          pb[v >> 3][v & 7] = (__bf16)p;
-        }
-      };
-      probs();
-      if (__any(psum > kLazySum)) {
-        const float m_new = fmaxf(m_run, row_max(s) * sc);
-        const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
-        l_run *= alpha;
-#pragma unroll
-        for (int dt = 0; dt < C::kDtiles; ++dt)
-#pragma unroll
-          for (int v = 0; v < 16; ++v) oacc[dt][v] *= alpha;
-        m_run = m_new;
-        probs();
-      }
-      l_run += psum;
-#pragma unroll
-      for (int m = 0; m < 2; ++m)
-#pragma unroll
-        for (int dt = 0; dt < C::kDtiles; ++dt)
-          oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vop[m * C::kDtiles + dt], pb[m], oacc[dt], 0, 0, 0);
+        for (int v = 0; v < 16; ++v) oacc[i][dt][v] *= alpha;
+      o_ready(i);
+      m_run[i] = m_new;
+      psum = probs(mode, i, mk);
     }
+    l_run[i] += psum;
+  };
+  // The reference a row starts from: its largest score of sub-tile 0.
+  auto first_max = [&](auto mode, int i, const Mask& mk) __attribute__((always_inline)) {
+    f32x16 s;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) s[v] = score(mode, i, v, mk);
+    m_run[i] = fmaxf(kMinit, row_max(s) * sc);
+  };
+
+  typedef std::integral_constant<int, 0> c_0;
+  // A phase: block i's products for sub-tiles j + 1 (scores) and j (output), and
+  // dealt between them block 1 - i's softmax (of sub-tile js) and
+  // whatever rest(c) adds behind MFMA c.
+  auto phase = [&](auto mask_c, const int i, int js, auto rest) __attribute__((always_inline)) {
+    constexpr int N = C::kMfma;
+    const int o = 1 - i;
+    float pr[16], psum = 0.f;
+    bool big = false;
+    const Mask mk = decltype(mask_c)::value ? mask_of(o, js) : Mask{-1, 64};
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int c = 0; c < N; ++c) {
+      // V's reads are half a phase old: one wait instead of one per operand
+      if (i == 0 && c == C::kKsteps) __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+      if (c < C::kKsteps)
+        mfma_s(i, c);
+      else
+        mfma_o(i, c - C::kKsteps);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int v = 0; v < 16; ++v)
+        if (v >= ct_exps(c - 1, N) && v < ct_exps(c, N)) {
+          pr[v] = __builtin_amdgcn_exp2f(fmaf(score(mask_c, o, v, mk), sc, -m_run[o]));
+        }
+#pragma unroll
+      for (int v = 0; v < 16; ++v)
+        if (v >= ct_exps(c - 2, N) && v < ct_exps(c - 1, N)) {
+          psum += pr[v];
+          if (v & 1) {
+            uint32_t w = focus::pack_bf16x2(pr[v - 1], pr[v]);
+            asm volatile("" : "+v"(w));  // (here, not behind the rescaling test)
+            pb[o][v >> 3][(v >> 1) & 3] = w;
+          }
+        }
+      if (c == N - 1) big = __any(psum > kLazySum);
+      rest(c);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    settle(mask_c, o, psum, big, mk);
+  };
+  // Phase A of sub-tile j (the half K0 of src's copies, K or V, go to stage cst) ...
+  auto phase_a = [&](auto mask_c, int j, const Src* src, int cst, auto k0_c) __attribute__((always_inline)) {
+    constexpr int kEach = C::kMfma / C::kDma, k0 = decltype(k0_c)::value;
+    phase(mask_c, 0, j, [&](int c) __attribute__((always_inline)) {
+      if (src)
+        each<C::kDma>([&](auto k) __attribute__((always_inline)) {
+          if (c == decltype(k)::value * kEach + 1)
+            issue(*src, cst, std::integral_constant<int, k0 + decltype(k)::value>(), false);
+        });
+    });
+  };
+  // ... and phase B: the next K and V operands (of the given halves) replace the
+  // used ones.
+  auto phase_b = [&](auto mask_c, int j, const int hk2, const int hv) __attribute__((always_inline)) {
+    phase(mask_c, 1, j + 1, [&](int c) __attribute__((always_inline)) {
+      c < C::kKsteps ? read_k(hk2, c) : read_v(hv, c - C::kKsteps);
+    });
   };
 
   // vmcnt(n): this wave's copies older than its last n have landed
@@ -1314,32 +1437,47 @@ __global__ __launch_bounds__(512, 2) void attn_ct(
       __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));  // vmcnt(0)
     __builtin_amdgcn_s_barrier();
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    __builtin_amdgcn_sched_barrier(0);
   };
-  // step u: sub-tiles 2u, 2u + 1 from tile u (V in vc); K of tile u + 1
-  // (kn); copies of tile u + 3 into (kcp, vcp), the buffers tile u - 1 left.
-  // A clean step (fast = true) has every sub-tile live and unmasked for every
-  // wave and copies a full tile; it runs without any branch but the softmax's
-  // rescaling test.
-  auto step = [&](int u, const char* vc, const char* kn, char* kcp, char* vcp, const bool fast)
-      __attribute__((always_inline)) {
-    pin_offsets();
-    Src src;
-    if (fast) {
-      const int tg = tb + u + 3;
-      const int64_t off = (int64_t)tg * tstride;
-      const bool c = tg < nct;
-      src.k = (c ? kcache_b : kwin_b) + off;
-      src.v = (c ? vcache_b : vwin_b) + off;
-      src.lo = 0;
-      src.last = 0;
-      src.full = true;
-    } else {
-      src = tile_src(u + 3);
-    }
-    sub(2 * u, 0, fast, vc, kn, kcp, vcp, u, src);
-    sub(2 * u + 1, 1, fast, vc, kn, kcp, vcp, u, src);
+  // Step u: sub-tiles 2u, 2u + 1 from tile u in stage u mod 4; copies of tile
+  // u + 3 into the stage tile u - 1 left.  A clean step has every sub-tile it
+  // touches (2u .. 2u + 2) unmasked for every wave and copies a full tile; it
+  // runs without any branch but the softmax's rescaling test (a block 1 without a
+  // query computes what nobody uses; a wave without any only copies).
+  auto advance_k = [&](int st) __attribute__((always_inline)) {
+#pragma unroll
+    for (int s = 0; s < C::kKsteps; ++s) next_stage(kofs[s], st);
+  };
+  auto advance_v = [&](int st) __attribute__((always_inline)) {
+#pragma unroll
+    for (int dt = 0; dt < C::kDtiles; ++dt) next_stage(vofs[dt], st);
+  };
+  auto clean_step = [&](int u) __attribute__((always_inline)) {
+    const int st = u & 3, cst = (u + 3) & 3;
+    const int tg = tb + u + 3;
+    const int64_t off = (int64_t)tg * tstride;
+    const Src src = {(tg < nct ? kcache_b : kwin_b) + off, (tg < nct ? vcache_b : vwin_b) + off, 0, 0};
+    advance_k(st);
+    phase_a(mask_none(), 2 * u, &src, cst, c_0());
+    phase_b(mask_none(), 2 * u, 0, 1);
+    phase_a(mask_none(), 2 * u + 1, &src, cst, std::integral_constant<int, C::kDma>());
+    advance_v(st);
+    phase_b(mask_none(), 2 * u + 1, 1, 0);
     // step u + 1 reads K of tile u + 2: wait for it (tile u + 3 may stay in flight)
-    wait_copies(fast || u + 3 < ntiles);
+    wait_copies(true);
+  };
+  auto step = [&](int u, auto mask_c) __attribute__((always_inline)) {
+    if (u + 3 < ntiles) {
+      const Src src = tile_src(u + 3);
+      issue_tile(src, (u + 3) & 3);
+    }
+    advance_k(u & 3);
+    phase_a(mask_c, 2 * u, nullptr, 0, c_0());
+    phase_b(mask_c, 2 * u, 0, 1);
+    phase_a(mask_c, 2 * u + 1, nullptr, 0, c_0());
+    advance_v(u & 3);
+    phase_b(mask_c, 2 * u + 1, 1, 0);
+    wait_copies(u + 3 < ntiles);
   };
 
   // The scale arrives by a scalar load whose first use is inside the loop;
@@ -1349,96 +1487,116 @@ __global__ __launch_bounds__(512, 2) void attn_ct(
   // Clean steps: tiles tb + u fully visible to the block's first query (the
   // cache tiles past a partial tile 0, the window tiles below the block's
   // rows) whose copy, tile u + 3, is a full tile; they form one run
-  // [u0, u1).  Tile u sits in stage (u - u0) mod 4, so the run starts on stage
-  // 0; a partial tile 0 (u0 = 1) takes stage 3 and the general step.  The
-  // run goes in rounds of four, its last (u1 - u0) mod 4 steps and the
-  // diagonal band after it in the general loop.
+  // [u0, u1), the last of which also touches the next tile's first sub-tile
+  // (block 0's softmax), so that tile has to be unmasked for block 0: window
+  // rows up to q0 + 31, below its rows from q0 + 128 on.
   const int u0 = (tb == 0 && pad > 0 && ntiles > 0) ? 1 : 0;
   const int u1 = max(u0, min(min(nct + (q0 + 1) / C::kBK, wfull - 3) - tb, ntiles - 3));
-  const int nclean = (u1 - u0) & ~3;
-  // prologue: tiles 0..2 in flight, wait for 0 and 1
-  {
-    const Src s0 = tile_src(0), s1 = tile_src(1), s2 = tile_src(2);
-    if (u0 == 0) {
+  // prologue: tiles 0..2 in flight, wait for 0 and 1; scores of sub-tile 0 and
+  // block 0's softmax of it, K of sub-tile 1, V of sub-tile 0
 #pragma unroll
-      for (int i = 0; i < C::kDma; ++i) {
-        if (ntiles > 0) issue(s0, kb0, vb0, i, !s0.full);
-        if (ntiles > 1) issue(s1, kb1, vb1, i, !s1.full);
-        if (ntiles > 2) issue(s2, kb2, vb2, i, !s2.full);
-      }
-      wait_copies(ntiles > 2);
-      read_k(kb0, 0);
-      if (0 < jlive) qk(sacc[0]);
-      read_k(kb0, 1);
-    } else {
+  for (int t = 0; t < 3; ++t) {
+    const Src src = tile_src(t);
+    if (t < ntiles) issue_tile(src, t);
+    // Q's loads are older than the copies: both land here (the compiler, which
+    // does not see the copies, would wait for all of them at Q's first use)
+    if (t == 1) {
+      o_ready(0);  // (oacc is cleared here, while they are on their way)
+      o_ready(1);
+      __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));  // vmcnt(0)
 #pragma unroll
-      for (int i = 0; i < C::kDma; ++i) {
-        issue(s0, kb3, vb3, i, true);
-        if (ntiles > 1) issue(s1, kb0, vb0, i, !s1.full);
-        if (ntiles > 2) issue(s2, kb1, vb1, i, !s2.full);
-      }
-      wait_copies(ntiles > 2);
-      read_k(kb3, 0);
-      if (0 < jlive) qk(sacc[0]);
-      read_k(kb3, 1);
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int s = 0; s < C::kKsteps; ++s) asm volatile("" : "+v"(qf[i][s]));
     }
   }
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+  __builtin_amdgcn_s_barrier();
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+  // A wave whose rows all lie past the window's end only copies.
+  if (wq[1] >= T) {
+    for (int u = 0; u < ntiles; ++u) {
+      if (u + 3 < ntiles) issue_tile(tile_src(u + 3), (u + 3) & 3);
+      wait_copies(u + 3 < ntiles);
+    }
+    return;
+  }
+#pragma unroll
+  for (int s = 0; s < C::kKsteps; ++s) read_k(0, s);
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int s = 0; s < C::kKsteps; ++s) mfma_s(i, s);
+#pragma unroll
+  for (int s = 0; s < C::kKsteps; ++s) read_k(1, s);
+#pragma unroll
+  for (int x = 0; x < 2 * C::kDtiles; ++x) read_v(0, x);
+  // (the output accumulators are still zero: nothing to rescale)
+  first_max(mask_lo_hi(), 0, mask_of(0, 0));
+  first_max(mask_lo_hi(), 1, mask_of(1, 0));
+  l_run[0] = probs(mask_lo_hi(), 0, mask_of(0, 0));
   // Let every scalar load land before the loop (lgkmcnt(0) once): a scalar
   // load still pending there would make the compiler wait for all LDS reads
   // at every counter wait inside the loop.
   __builtin_amdgcn_s_waitcnt(0xC07F);
   int u = 0;
-  if (u0 > 0) {
-    step(0, vb3, kb0, kb2, vb2, false);
-    u = 1;
-  }
-  for (; u < u0 + nclean; u += 4) {
-    step(u, vb0, kb1, kb3, vb3, true);
-    step(u + 1, vb1, kb2, kb0, vb0, true);
-    step(u + 2, vb2, kb3, kb1, vb1, true);
-    step(u + 3, vb3, kb0, kb2, vb2, true);
-  }
-  for (; u < ntiles; u += 4) {
-    step(u, vb0, kb1, kb3, vb3, false);
-    if (u + 1 >= ntiles) break;
-    step(u + 1, vb1, kb2, kb0, vb0, false);
-    if (u + 2 >= ntiles) break;
-    step(u + 2, vb2, kb3, kb1, vb1, false);
-    if (u + 3 >= ntiles) break;
-    step(u + 3, vb3, kb0, kb2, vb2, false);
-  }
+  if (u0 > 0) step(u++, mask_lo_hi());
+  for (; u < u1; ++u) clean_step(u);
+  for (; u < ntiles; ++u) step(u, mask_hi());
 
-  const float l_tot = l_run + __shfl_xor(l_run, 32);
-  if (sp.n > 1) {
-    // key split: the unnormalised output and (max, sum) of this tile range
-    if (qi < T && qi < sp.rows) {
-      const int64_t pidx = (((int64_t)split * sp.nwl + it.list_idx) * sp.rows + qi) * H + h;
-      float* op = sp.po + pidx * D;
 #pragma unroll
-      for (int dt = 0; dt < C::kDtiles; ++dt)
+  for (int i = 0; i < 2; ++i) {
+    o_ready(i);
+    const float l_tot = l_run[i] + __shfl_xor(l_run[i], 32);
+    if (qi[i] >= T) continue;
+    if (sp.n > 1) {
+      // key split: the unnormalised output and (max, sum) of this tile range
+      if (qi[i] < sp.rows) {
+        const int64_t pidx = (((int64_t)split * sp.nwl + li) * sp.rows + qi[i]) * H + h;
+        float* op = sp.po + pidx * D;
 #pragma unroll
-        for (int v4 = 0; v4 < 4; ++v4)
-          *reinterpret_cast<float4*>(op + 32 * dt + 8 * v4 + 4 * g) =
-              make_float4(oacc[dt][4 * v4], oacc[dt][4 * v4 + 1], oacc[dt][4 * v4 + 2], oacc[dt][4 * v4 + 3]);
-      if (g == 0) *reinterpret_cast<float2*>(sp.pml + pidx * 2) = make_float2(m_run, l_tot);
+        for (int dt = 0; dt < C::kDtiles; ++dt)
+#pragma unroll
+          for (int v4 = 0; v4 < 4; ++v4)
+            *reinterpret_cast<float4*>(op + 32 * dt + 8 * v4 + 4 * g) =
+                make_float4(oacc[i][dt][4 * v4], oacc[i][dt][4 * v4 + 1], oacc[i][dt][4 * v4 + 2], oacc[i][dt][4 * v4 + 3]);
+        if (g == 0) *reinterpret_cast<float2*>(sp.pml + pidx * 2) = make_float2(m_run[i], l_tot);
+      }
+      continue;
     }
-    return;
+    if (g == 0 && d.lse) d.lse[(tok0 + qi[i]) * H + h] = (m_run[i] + log2f(l_tot)) * kLn2;
   }
-  if (qi < T) {
-    const float inv = 1.f / l_tot;
-    const int64_t orow = tok0 + qi;
-    __bf16* op = reinterpret_cast<__bf16*>(d.o) + (orow * H + h) * D;
+  if (sp.n > 1) return;
+  // O through this wave's part of the (now free) stages, 16-byte chunk c of row r
+  // at c ^ (r mod kCh16), so that a store writes whole rows: 8 bytes a lane of 32
+  // rows each took 4.2 us of a workgroup's 45 at 100 kb.
+  char* ow = lds + wave * 64 * C::kRB;
+  typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+  typedef __attribute__((address_space(3))) u32x2 lds_u2;
+  typedef __attribute__((address_space(3))) u32x4 lds_u4;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const float inv = 1.f / (l_run[i] + __shfl_xor(l_run[i], 32));
+    const int row = 32 * i + l32;
 #pragma unroll
     for (int dt = 0; dt < C::kDtiles; ++dt)
 #pragma unroll
       for (int v4 = 0; v4 < 4; ++v4) {
-        // oacc[dt][4 v4 + e] = O[qi][32 dt + 8 v4 + 4 g + e]
-        uint2 w;
-        w.x = focus::pack_bf16x2(oacc[dt][4 * v4 + 0] * inv, oacc[dt][4 * v4 + 1] * inv);
-        w.y = focus::pack_bf16x2(oacc[dt][4 * v4 + 2] * inv, oacc[dt][4 * v4 + 3] * inv);
-        *reinterpret_cast<uint2*>(op + 32 * dt + 8 * v4 + 4 * g) = w;
+        // oacc[i][dt][4 v4 + e] = O[qi][32 dt + 8 v4 + 4 g + e]
+        u32x2 w;
+        w.x = focus::pack_bf16x2(oacc[i][dt][4 * v4 + 0] * inv, oacc[i][dt][4 * v4 + 1] * inv);
+        w.y = focus::pack_bf16x2(oacc[i][dt][4 * v4 + 2] * inv, oacc[i][dt][4 * v4 + 3] * inv);
+        *(lds_u2*)(uintptr_t)(lds_addr(ow) + row * C::kRB + (((4 * dt + v4) ^ (row & (C::kCh16 - 1))) << 4) + 8 * g) = w;
       }
-    if (g == 0 && d.lse) d.lse[orow * H + h] = (m_run + log2f(l_tot)) * kLn2;
+  }
+  constexpr int kRows = 64 / C::kCh16;  // rows a store of the wave covers
+#pragma unroll
+  for (int x = 0; x < 64 / kRows; ++x) {
+    const int row = x * kRows + lane / C::kCh16, c = lane % C::kCh16;
+    const int q = wq[x * kRows / 32] + row % 32;
+    const u32x4 w = *(const lds_u4*)(uintptr_t)(lds_addr(ow) + row * C::kRB + ((c ^ (row & (C::kCh16 - 1))) << 4));
+    if (q < T)
+      *reinterpret_cast<u32x4*>(reinterpret_cast<__bf16*>(d.o) + ((tok0 + q) * H + h) * D + 8 * c) = w;
   }
 }
 
@@ -2150,7 +2308,8 @@ __global__ __launch_bounds__(64 * kF32Waves, D == 64 ? 2 : 1) void attn_f32(focu
 
 // Query tile rows of a launch: 32 per computing wave (bf16), kF32Rows (f32).
 int attn_rows_per_tile(const focus_attn_desc* d) {
-  return d->dtype == FOCUS_BF16 ? 32 * (d->mask == FOCUS_MASK_KMER_LOCAL ? kBf16WavesKL : kBf16Waves) : kF32Rows;
+  if (d->dtype == FOCUS_F32) return kF32Rows;
+  return d->mask == FOCUS_MASK_KMER_LOCAL ? 32 * kBf16WavesKL : kCtRows;
 }
 
 // Key splits of a C(t) bf16 launch (1 = none): as many as still fit the
@@ -2212,7 +2371,7 @@ extern "C" focus_status focus_window_attn(const focus_attn_desc* d, focus_stream
   const float sc = scale * kLog2e;
   const int64_t n_pairs = nwl * d->n_heads;
   const bool kl = d->mask == FOCUS_MASK_KMER_LOCAL;
-  const int waves = kl ? kBf16WavesKL : kBf16Waves;
+  const int waves = kl ? kBf16WavesKL : kCtWaves;
   const int bq = attn_rows_per_tile(d);
   const int threads = 64 * (d->dtype == FOCUS_BF16 ? waves : kF32Waves);
   const int64_t qt = focus::ceil_div(t.max_window_tokens, bq);
@@ -2230,7 +2389,7 @@ extern "C" focus_status focus_window_attn(const focus_attn_desc* d, focus_stream
   const int64_t n_pairs8 = focus::ceil_div(n_pairs, focus::kXcds) * focus::kXcds, blocks = n_pairs8 * qt * sp.n;
   // (f32: the limit counts 64-row tiles; the grid of its smaller ones has a second dimension)
   const int64_t lim = d->dtype == FOCUS_F32 ? n_pairs8 * focus::ceil_div(t.max_window_tokens, 64) : blocks;
-  if (lim * threads >= ((int64_t)1 << 32) || qt > INT32_MAX) return FOCUS_E_SHAPE;
+  if (lim * (d->dtype == FOCUS_BF16 && !kl ? 512 : threads) >= ((int64_t)1 << 32) || qt > INT32_MAX) return FOCUS_E_SHAPE;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   dim3 grid((uint32_t)blocks), block(threads);
   if (d->dtype == FOCUS_F32 && blocks >= (1 << 20))

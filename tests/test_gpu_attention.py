@@ -401,3 +401,22 @@ def test_f32_tile_edges(L, W, kmer, D):
     ref = build_layout([L], W, km)
     p = Prefill([L], W, km, 3, 1, D, "f32", seed=64)
     compare_windows(ref, p, range(ref["n_windows"]), [0, 1, 2], "f32 tile edges")
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("W,k,seq", [
+    (40, 8, [400]),          # one 45-row query tile: three waves of the tile without a row
+    (255, 300, [1020]),      # exactly one query tile of 256 rows
+    (256, 256, [1500]),      # 257 rows: the second query tile has one
+    (300, 10, [3000]),       # 330 rows; cache lengths 0 .. 270 in steps of 30
+    (470, 47, [4700]),       # 480 rows: blocks past the window's end in some waves only
+    (700, 100, [5000, 33]),  # a 3-tile window, a truncated one and a one-tile sequence
+])
+def test_ct_query_and_key_tile_edges(W, k, seq, D):
+    """bf16 windows whose rows end on and around the 32-row query blocks and the
+    256-row tiles, with cache lengths that leave every kind of first key tile."""
+    announce(f"attn ct tile edges W={W} k={k} seq={seq} D={D}")
+    km = np.full(sum(-(-n // W) for n in seq), k, np.int32)
+    ref = build_layout(seq, W, km)
+    p = Prefill(seq, W, km, 8, 4, D, "bf16", seed=65)
+    compare_windows(ref, p, range(ref["n_windows"]), [0, 3, 7], "ct tile edges")

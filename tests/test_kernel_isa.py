@@ -125,3 +125,45 @@ def test_no_spills_and_no_compiler_wait_before_lds_reads(asm, head_dim):
         if prev is not None and prev.startswith("s_waitcnt") and "vmcnt" in prev:
             assert not s.startswith(("ds_read", "v_mfma")), f"compiler wait before an LDS read: {prev} -> {s}"
         prev = s
+
+
+# attn_ct keeps its output accumulators in AGPRs through inline-assembly MFMAs,
+# whose latency the compiler does not know: any other access to an AGPR must
+# come after the kernel's own wait states (s_nop 15), and the phases (blocks with
+# a row of MFMAs) must leave the AGPRs, the copies' counter and scratch alone.
+CT_KERNELS = ["_ZN12_GLOBAL__N_17attn_ctILi128EEEv15focus_attn_descfliNS_5SplitE",
+              "_ZN12_GLOBAL__N_17attn_ctILi64EEEv15focus_attn_descfliNS_5SplitE"]
+
+
+@pytest.mark.parametrize("name", CT_KERNELS)
+def test_ct_accumulators_touched_only_behind_wait_states(asm, name):
+    i = next(k for k, line in enumerate(asm) if re.search(r"\.name:\s+" + re.escape(name) + r"$", line))
+    spill = next(line for line in asm[i:] if ".vgpr_spill_count:" in line)
+    assert int(spill.split(":")[1]) == 0, spill
+    start, end = _body(asm, name)
+    pending, blocks, block = False, 0, []
+
+    def close():
+        mfmas = [x for x in block if x.startswith("v_mfma")]
+        if len(mfmas) < 8 or any(x.startswith("s_barrier") for x in block):
+            return 0
+        bad = [x for x in block if x.startswith(("v_accvgpr", "scratch_", "s_nop 15")) or "vmcnt" in x]
+        assert not bad, bad
+        return 1
+
+    for line in asm[start:end]:
+        s = line.strip()
+        if s.startswith(".LBB"):
+            blocks += close()
+            block = []
+        if not s or s.startswith((";", ".")) or s.endswith(":"):
+            continue
+        block.append(s)
+        if s.startswith("v_mfma") and s.split()[1].startswith("a["):
+            pending = True
+        elif s.startswith("s_nop 15"):
+            pending = False
+        elif s.startswith("v_accvgpr"):
+            assert not pending, s
+    blocks += close()
+    assert blocks >= 12, blocks  # four clean phases, eight masked ones
