@@ -72,10 +72,22 @@ def _ptr_rows(t) -> int:
     return t.data_ptr()
 
 
+# Handle of a device's current stream without the Stream object around it (0.1
+# against 1.8 us a call), where this torch has it.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream, device) -> int:
     if stream is None:
+        if _raw_stream is not None and device.index is not None:
+            return _raw_stream(device.index)
         stream = torch.cuda.current_stream(device)
     return stream.cuda_stream
+
+
+# The descriptors below are filled by position, in the order of their fields in
+# _abi.py: ctypes then sets all of them in C (0.5 us for a decode step's 26 fields;
+# one attribute assignment each took 3).
 
 
 def _scratch(nbytes: int, device, stream):
@@ -171,55 +183,38 @@ def focus_compact_kv(lay: Layout, k, v, cache_k, cache_v, cache_len=None, win_id
                      kv_tok_base: int = 0, err=None, stream=None):
     """Append the summary K/V rows of the listed windows (all if win_ids is None)
     to cache_k / cache_v [batch, cap, H_kv, D]; raise cache_len."""
-    d = CompactDesc()
-    d.totals = lay.totals
-    d.dtype = _dtype(k)
-    d.n_kv_heads, d.head_dim = k.shape[1], k.shape[2]
-    d.batch = lay.batch
-    d.n_win = 0 if win_ids is None else win_ids.numel()
-    d.win_ids = _ptr(win_ids)
-    for f in ("win_seq", "win_nsum", "win_cache_off", "win_sum_off", "sum_tok"):
-        setattr(d, f, _ptr(lay[f]))
-    d.k, d.v, d.kv_tok_base, d.kv_rows = _ptr(k), _ptr(v), int(kv_tok_base), k.shape[0]
+    kp = _ptr(k)
     if (cache_k.shape != cache_v.shape or cache_k.dtype != k.dtype or cache_k.shape[2:] != k.shape[1:]
             or cache_k.shape[0] < lay.batch or v.shape != k.shape):
         raise ValueError("cache shape/dtype does not match k, or holds fewer sequences than the layout")
     if cache_len is not None and cache_len.numel() < lay.batch:
         raise ValueError("cache_len needs one entry per sequence")
-    d.cache_k, d.cache_v, d.cache_cap = _ptr(cache_k), _ptr(cache_v), cache_k.shape[1]
-    d.cache_len, d.err = _ptr(cache_len), _ptr(err)
+    arr = lay.arrays
+    d = CompactDesc(lay.totals, _dtype(k), k.shape[1], k.shape[2], lay.batch, 0 if win_ids is None else win_ids.numel(),
+                    _ptr(win_ids), _ptr(arr["win_seq"]), _ptr(arr["win_nsum"]), _ptr(arr["win_cache_off"]),
+                    _ptr(arr["win_sum_off"]), _ptr(arr["sum_tok"]), kp, _ptr(v), int(kv_tok_base), k.shape[0],
+                    _ptr(cache_k), _ptr(cache_v), cache_k.shape[1], _ptr(cache_len), _ptr(err))
     check("focus_compact_kv", lib().focus_compact_kv(C.byref(d), _stream(stream, k.device)))
 
 
 def _attn_desc(lay, q, k, v, cache_k, cache_v, o, lse, win_ids, qkv_tok_base, softmax_scale, mask,
                workspace, err):
-    d = AttnDesc()
-    d.totals = lay.totals
-    d.dtype = _dtype(q)
-    d.n_heads, d.head_dim = q.shape[1], q.shape[2]
-    d.n_kv_heads = k.shape[1]
-    d.softmax_scale = float(softmax_scale)
-    d.mask = int(mask)
-    d.batch = lay.batch
-    d.kmer_uniform = int(lay.kmer_uniform)
-    d.win_kmer = _ptr(lay.kmer)
-    d.n_win = 0 if win_ids is None else win_ids.numel()
-    d.win_ids = _ptr(win_ids)
-    for f in ("win_seq", "win_ntok", "win_cache_off", "win_tok_off"):
-        setattr(d, f, _ptr(lay[f]))
     if not (q.dtype == k.dtype == v.dtype) or k.shape != v.shape or q.shape[0] != k.shape[0]:
         raise ValueError("q/k/v shapes or dtypes disagree")
-    d.q, d.k, d.v, d.qkv_tok_base, d.qkv_rows = _ptr(q), _ptr(k), _ptr(v), int(qkv_tok_base), q.shape[0]
     if cache_k is not None:
         if (cache_k.dtype != q.dtype or cache_k.shape[2:] != k.shape[1:] or cache_k.shape != cache_v.shape
                 or cache_k.shape[0] < lay.batch):
             raise ValueError("cache shape/dtype does not match k, or holds fewer sequences than the layout")
-        d.cache_k, d.cache_v, d.cache_cap = _ptr(cache_k), _ptr(cache_v), cache_k.shape[1]
-    d.o, d.lse = _ptr(o), _ptr(lse)
-    d.workspace = _ptr(workspace)
-    d.workspace_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    d.err = _ptr(err)
-    return d
+        cache = _ptr(cache_k), _ptr(cache_v), cache_k.shape[1]
+    else:
+        cache = None, None, 0
+    arr = lay.arrays
+    return AttnDesc(lay.totals, _dtype(q), q.shape[1], k.shape[1], q.shape[2], float(softmax_scale), int(mask), lay.batch,
+                    int(lay.kmer_uniform), 0 if win_ids is None else win_ids.numel(), _ptr(win_ids),
+                    _ptr(arr["win_seq"]), _ptr(arr["win_ntok"]), _ptr(arr["win_cache_off"]),
+                    _ptr(arr["win_tok_off"]), _ptr(lay.kmer), _ptr(q), _ptr(k), _ptr(v), int(qkv_tok_base), q.shape[0],
+                    *cache, _ptr(o), _ptr(lse), _ptr(workspace),
+                    0 if workspace is None else workspace.numel() * workspace.element_size(), _ptr(err))
 
 
 def focus_window_attn_workspace(lay: Layout, q, k, v, cache_k=None, cache_v=None, win_ids=None,
@@ -242,32 +237,26 @@ def focus_window_attn(lay: Layout, q, k, v, cache_k=None, cache_v=None, o=None, 
         lse = torch.empty(q.shape[0], q.shape[1], dtype=torch.float32, device=q.device)
     if o.shape != q.shape or o.dtype != q.dtype or (lse is not None and tuple(lse.shape) != tuple(q.shape[:2])):
         raise ValueError("o must match q; lse must be [rows, heads]")
-    if workspace is None:
-        # key-split scratch for launches that would leave compute units idle
-        n = focus_window_attn_workspace(lay, q, k, v, cache_k, cache_v, win_ids, mask)
-        workspace = _scratch(n, q.device, stream) if n > 0 else None
     d = _attn_desc(lay, q, k, v, cache_k, cache_v, o, lse, win_ids, qkv_tok_base, softmax_scale,
                    mask, workspace, err)
+    if workspace is None:
+        # key-split scratch for launches that would leave compute units idle
+        n = lib().focus_window_attn_workspace(C.byref(d))
+        if n > 0:
+            workspace = _scratch(n, q.device, stream)
+            d.workspace, d.workspace_bytes = workspace.data_ptr(), n
     check("focus_window_attn", lib().focus_window_attn(C.byref(d), _stream(stream, q.device)))
     return o, lse
 
 
 def _decode_desc(q, k_new, v_new, kind, cache_k, cache_v, cache_len, win_k, win_v, win_len,
                  o, lse, workspace, split_keys, softmax_scale, err):
-    d = DecodeDesc()
-    d.dtype = _dtype(q)
-    d.batch, d.n_heads, d.head_dim = q.shape
-    d.n_kv_heads = k_new.shape[1]
-    d.softmax_scale = float(softmax_scale)
-    d.split_keys = int(split_keys)
-    d.q, d.k_new, d.v_new, d.kind = _ptr(q), _ptr(k_new), _ptr(v_new), _ptr(kind)
-    d.cache_k, d.cache_v, d.cache_cap, d.cache_len = _ptr(cache_k), _ptr(cache_v), cache_k.shape[1], _ptr(cache_len)
-    d.win_k, d.win_v, d.win_cap, d.win_len = _ptr(win_k), _ptr(win_v), win_k.shape[1], _ptr(win_len)
-    d.o, d.lse = _ptr(o), _ptr(lse)
-    d.workspace = _ptr(workspace)
-    d.workspace_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    d.err = _ptr(err)
-    return d
+    batch, heads, dim = q.shape
+    return DecodeDesc(_dtype(q), batch, heads, k_new.shape[1], dim, float(softmax_scale), int(split_keys), 0,
+                      _ptr(q), _ptr(k_new), _ptr(v_new), _ptr(kind), _ptr(cache_k), _ptr(cache_v), cache_k.shape[1],
+                      _ptr(cache_len), _ptr(win_k), _ptr(win_v), win_k.shape[1], _ptr(win_len), _ptr(o), _ptr(lse),
+                      _ptr(workspace), 0 if workspace is None else workspace.numel() * workspace.element_size(),
+                      _ptr(err))
 
 
 def focus_decode_workspace(q, k_new, cache_k, win_k, split_keys: int = 0) -> int:
@@ -333,14 +322,10 @@ class DecodeSchedule:
         self.err = err
 
     def _desc(self, tokens=None):
-        d = DecodeSched()
-        d.batch, d.window_nt, d.kmer_uniform = self.batch, self.window_nt, self.kmer_uniform
-        d.kmer_stride = 0 if self.kmer is None else self.kmer.shape[1]
-        d.kmer = _ptr(self.kmer)
-        d.win_index, d.bases_in_window = _ptr(self.win_index), _ptr(self.bases_in_window)
-        d.bases_in_kmer, d.kind = _ptr(self.bases_in_kmer), _ptr(self.kind)
-        d.tokens, d.summaries, d.err = _ptr(tokens), _ptr(self.summaries), _ptr(self.err)
-        return d
+        return DecodeSched(self.batch, self.window_nt, self.kmer_uniform,
+                           0 if self.kmer is None else self.kmer.shape[1], _ptr(self.kmer), _ptr(self.win_index),
+                           _ptr(self.bases_in_window), _ptr(self.bases_in_kmer), _ptr(self.kind), _ptr(tokens),
+                           _ptr(self.summaries), _ptr(self.err))
 
     def start(self, tokens, stream=None):
         """Walk tokens[b] tokens into each sequence's current window; returns
@@ -426,13 +411,8 @@ def focus_gemm(a, b, out=None, a_rows=None, alpha: float = 1.0, out_dtype=torch.
         out = torch.empty(m, n, dtype=out_dtype, device=a.device)
     if tuple(out.shape) != (m, n) or out.stride(1) != 1:
         raise ValueError("out must be [m, n] row-major")
-    d = GemmDesc()
-    d.m, d.n, d.k = m, n, a.shape[1]
-    d.a, d.lda, d.a_rows, d.a_nrows = _ptr_rows(a), a.stride(0), _ptr(a_rows), a.shape[0]
-    d.b, d.ldb = _ptr_rows(b), b.stride(0)
-    d.c, d.ldc, d.c_dtype = _ptr_rows(out), out.stride(0), _dtype(out)
-    d.alpha = float(alpha)
-    d.err = _ptr(err)
+    d = GemmDesc(m, n, a.shape[1], _ptr_rows(a), a.stride(0), _ptr(a_rows), a.shape[0], _ptr_rows(b), b.stride(0),
+                 _ptr_rows(out), out.stride(0), _dtype(out), float(alpha), _ptr(err))
     check("focus_gemm", lib().focus_gemm(C.byref(d), _stream(stream, a.device)))
     return out
 
