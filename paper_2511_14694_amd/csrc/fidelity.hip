@@ -339,9 +339,15 @@ __device__ inline float half_min(float x) { return -half_max(-x); }
 //   (decided from the row minimum of the logits), the clip changes nothing and
 //   the renormalised sum is 1: that pass is skipped.  Otherwise the clip and
 //   the renormalisation are applied as in fid_rows_wave;
-// * log2 p and log2 q come from the logits, and the mixture's logarithm from
-//   r = log2 q - log2 p: log2 m - log2 p = max(r, 0) + log2((1 + 2^-|r|) / 2),
-//   so the JS term is q r - (p + q) that (exactly zero when p = q).
+// * KL and JS need only r = log2 q - log2 p, which comes from the logits: the
+//   mixture's log2 m - log2 p is log2((1 + 2^r) / 2) (|r| <= 40 within the
+//   clip), so the JS term is q r - (p + q) that (exactly zero when p = q);
+// * without the clip, both rows are taken in units of p's largest probability
+//   (p' = e_p^2, q' = (e_q s)^2 with s = sqrt(rq / rp)) and the sums scaled at
+//   the end: one product less per element.
+// Bound by the vector unit: 1 M x 512 bf16 with means 617 -> 584 us (one box)
+// against separate logarithms and scaled probabilities; eight positions per
+// half-wave with the next row prefetched took 7 % longer (fewer waves).
 template <typename T, int NPL, bool FULL>
 __global__ __launch_bounds__(kThreads) void fid_logits_half(focus_fidelity_desc d) {
   // every fused multiply-add below is written out: a product contracted into
@@ -411,27 +417,31 @@ __global__ __launch_bounds__(kThreads) void fid_logits_half(focus_fidelity_desc 
   const bool fast = emp * emp * rp >= 2.f * kClip && emq * emq * rq >= 2.f * kClip;
 
   float l1 = 0.f, l2 = 0.f, h = 0.f, js = 0.f, kl = 0.f;
-  // one pair: probabilities pn, qn, their square roots a, b and base-2 logs lp, lq
-  auto add = [&](float pn, float qn, float a, float b, float lp, float lq) __attribute__((always_inline)) {
+  // one pair: probabilities pn, qn, their square roots a, b and r = log2(qn / pn)
+  auto add = [&](float pn, float qn, float a, float b, float r) __attribute__((always_inline)) {
     const float dd = pn - qn;
     l1 += fabsf(dd);
     l2 = fmaf(dd, dd, l2);
     const float sd = a - b;
     h = fmaf(sd, sd, h);
-    const float r = lq - lp;
     kl = fmaf(pn, -r, kl);
-    const float g = fmaxf(r, 0.f) + __builtin_amdgcn_logf(fmaf(0.5f, __builtin_amdgcn_exp2f(-fabsf(r)), 0.5f));
+    const float g = __builtin_amdgcn_logf(fmaf(0.5f, __builtin_amdgcn_exp2f(r), 0.5f));
     js = fmaf(qn, r, js);
     js = fmaf(-(pn + qn), g, js);
   };
   if (fast) {
-    const float srp = __builtin_amdgcn_sqrtf(rp), srq = __builtin_amdgcn_sqrtf(rq);
+    const float s = __builtin_amdgcn_sqrtf(rq) / __builtin_amdgcn_sqrtf(rp), lr = lsp - lsq;
 #pragma unroll
     for (int k = 0; k < NPL; ++k) {
       if (!ok[k]) continue;
-      const float a = ep[k] * srp, b = eq[k] * srq;
-      add(a * a, b * b, a, b, fmaf(yp[k], 2.f, -lsp), fmaf(yq[k], 2.f, -lsq));
+      const float a = ep[k], b = eq[k] * s;
+      add(a * a, b * b, a, b, fmaf(yq[k] - yp[k], 2.f, lr));
     }
+    l1 *= rp;
+    l2 *= rp * rp;
+    h *= rp;
+    js *= rp;
+    kl *= rp;
   } else {
     // the clip at 1e-12 and the renormalisation, as in fid_rows_wave
     float p[NPL], q[NPL];
@@ -457,7 +467,7 @@ __global__ __launch_bounds__(kThreads) void fid_logits_half(focus_fidelity_desc 
       const float lp = (p[k] > kClip ? fmaf(yp[k], 2.f, -lsp) : lclip) - lcp;
       const float lq = (q[k] > kClip ? fmaf(yq[k], 2.f, -lsq) : lclip) - lcq;
       // pn, qn >= 1e-12 / 1.x: no denormals for the bare v_sqrt_f32
-      add(pn, qn, __builtin_amdgcn_sqrtf(pn), __builtin_amdgcn_sqrtf(qn), lp, lq);
+      add(pn, qn, __builtin_amdgcn_sqrtf(pn), __builtin_amdgcn_sqrtf(qn), lq - lp);
     }
   }
   Sums m;
