@@ -177,8 +177,12 @@ __global__ __launch_bounds__(kThreads) void decode_partial(focus_decode_desc d, 
     float acc = 0.f;
 #pragma unroll
     for (int e = 0; e < kEpt; ++e) acc = fmaf(q[e], kx[e], acc);
-    m = head_sum<TPH>(acc);
-    l = 1.f;
+    // (against the finite start: a score of -inf has weight 0, as in the chunks)
+    const float sn = head_sum<TPH>(acc);
+    m = fmaxf(m, sn);
+    l = __builtin_amdgcn_exp2f(sn - m);
+#pragma unroll
+    for (int e = 0; e < kEpt; ++e) o[e] *= l;
   }
   for (int j0 = jb; j0 < je; j0 += kChunk) {
     uint4 kr[kChunk][kU4], vr[kChunk][kU4];

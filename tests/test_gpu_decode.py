@@ -170,6 +170,62 @@ def test_decode_live_split_counts(splits, D):
         r.oracle(b, set(range(20)))
 
 
+class SmallStep:
+    """One base-token step of one sequence over 58 keys (37 cache rows, 20 window
+    rows, the step's own) in splits of 16, and its float64 value on the CPU."""
+    H, Hkv, CLEN, WLEN, KEYS = 4, 2, 37, 20, 58
+
+    def __init__(self, D, dtype, seed):
+        self.dtype = dtype
+        self.ck, self.cv = (fw.randn((1, 64, self.Hkv, D), dtype, seed + i, DEV) for i in range(2))
+        self.wk, self.wv = (fw.randn((1, 32, self.Hkv, D), dtype, seed + 2 + i, DEV) for i in range(2))
+        self.kn, self.vn = (fw.randn((1, self.Hkv, D), dtype, seed + 4 + i, DEV) for i in range(2))
+        self.q = fw.randn((1, self.H, D), dtype, seed + 6, DEV)
+
+    def row(self, j, values=False):
+        """K (or V) row [Hkv, D] of key j."""
+        c, w, n = (self.cv, self.wv, self.vn) if values else (self.ck, self.wk, self.kn)
+        return c[0, j] if j < self.CLEN else w[0, j - self.CLEN] if j < self.CLEN + self.WLEN else n[0]
+
+    def run(self):
+        cl, wl = (torch.tensor([n], dtype=torch.int32, device=DEV) for n in (self.CLEN, self.WLEN))
+        kind = torch.zeros(1, dtype=torch.uint8, device=DEV)
+        o, lse = F.focus_decode_step(self.q, self.kn, self.vn, kind, self.ck, self.cv, cl, self.wk, self.wv, wl,
+                                     split_keys=16)
+        torch.cuda.synchronize()
+        return o[0].double().cpu(), lse[0].double().cpu()
+
+    def check(self, o, lse):
+        """Against float64: sums of 58 keys in float32, o rounded to its type."""
+        k, v = (torch.stack([self.row(j, x) for j in range(self.KEYS)], 1).double().cpu()
+                .repeat_interleave(self.H // self.Hkv, 0) for x in (False, True))     # [H, keys, D]
+        q = self.q[0].double().cpu()
+        s = (k * q[:, None]).sum(-1) * q.shape[1] ** -0.5
+        ref = (torch.softmax(s, 1)[..., None] * v).sum(1)
+        torch.testing.assert_close(o, ref, rtol=2 ** -8 if self.dtype == "bf16" else 1e-5, atol=1e-5)
+        torch.testing.assert_close(lse, torch.logsumexp(s, 1), rtol=1e-5, atol=1e-5)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("D", [128, 64])
+def test_decode_scores_of_minus_infinity_have_weight_zero(D, dtype):
+    """-inf in one component of K where q is 1 makes the score -inf: the step's
+    own key alone, with every other key of its split (whose running maximum then
+    has no finite score to start from), and every key there is (o = 0, lse =
+    -inf: nothing has a weight)."""
+    for first in (57, 48, 0):
+        announce(f"decode -inf scores D={D} {dtype} keys {first} .. 57")
+        st = SmallStep(D, dtype, 51)
+        st.q[..., 0] = 1.0
+        for j in range(first, st.KEYS):
+            st.row(j)[:, 0] = -float("inf")
+        o, lse = st.run()
+        if first == 0:
+            assert (o == 0).all() and (lse == -float("inf")).all()
+        else:
+            st.check(o, lse)
+
+
 def test_decode_capacity_error():
     """A summary step into a full cache is skipped with FOCUS_ERR_CAPACITY; the
     step still attends over what is there and the length stays put."""
