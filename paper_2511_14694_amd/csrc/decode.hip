@@ -197,6 +197,15 @@ __global__ __launch_bounds__(kThreads) void decode_partial(focus_decode_desc d, 
         vr[u][i] = vp[i];
       }
     }
+    // Rows past the split's end repeat its last one with weight zero; their V is
+    // cleared, since zero times an infinity in it would be a NaN.
+    if (j0 + kChunk > je) {
+#pragma unroll
+      for (int u = 0; u < kChunk; ++u)
+        if (j0 + u >= je)
+#pragma unroll
+          for (int i = 0; i < kU4; ++i) vr[u][i] = make_uint4(0, 0, 0, 0);
+    }
     float s[kChunk];
 #pragma unroll
     for (int u = 0; u < kChunk; ++u) {
@@ -280,7 +289,11 @@ __global__ __launch_bounds__(D) void decode_combine(focus_decode_desc d, int spl
     }
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u) {
-      const float w = c0 + u * kGroups < ns ? __builtin_amdgcn_exp2f(x[u].x - M) : 0.f;
+      // past the last split: it again, as zeros with weight zero (zero times an
+      // infinity in V would be a NaN)
+      const bool in = c0 + u * kGroups < ns;
+      const float w = in ? __builtin_amdgcn_exp2f(x[u].x - M) : 0.f;
+      y[u] = in ? y[u] : make_float4(0.f, 0.f, 0.f, 0.f);
       L = fmaf(x[u].y, w, L);
       o.x = fmaf(y[u].x, w, o.x);
       o.y = fmaf(y[u].y, w, o.y);

@@ -226,6 +226,26 @@ def test_decode_scores_of_minus_infinity_have_weight_zero(D, dtype):
             st.check(o, lse)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("D", [128, 64])
+def test_decode_infinity_in_v_is_an_infinity(D, dtype):
+    """An infinity in one component of one key's V makes that component of the
+    heads that read it infinite and changes nothing else, wherever the key sits:
+    the first and last of a split, of the cache, of the window, of the last split
+    (loads past a split's end and past the last split repeat their last row)."""
+    st = SmallStep(D, dtype, 71)
+    o0, lse0 = st.run()
+    st.check(o0, lse0)
+    for j in (0, 15, 16, 36, 37, 47, 48, 55, 56, 57):
+        announce(f"decode infinite V D={D} {dtype} key {j}")
+        st = SmallStep(D, dtype, 71)
+        st.row(j, values=True)[1, 5] = -float("inf")
+        o, lse = st.run()
+        want = o0.clone()
+        want[2:, 5] = -float("inf")
+        assert torch.equal(lse, lse0) and torch.equal(o, want)
+
+
 def test_decode_capacity_error():
     """A summary step into a full cache is skipped with FOCUS_ERR_CAPACITY; the
     step still attends over what is there and the length stays put."""
