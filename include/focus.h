@@ -245,6 +245,9 @@ focus_status focus_compact_kv(const focus_compact_desc* d, focus_stream_t stream
  * (k-mer j of a window with cadence k spans window rows [j (k+1), j (k+1) + k],
  * its summary last, as focus_layout places them) and needs each window's k:
  * win_kmer (the per-window array given to focus_layout) or kmer_uniform.
+ * An infinity or NaN in V reaches only the rows whose visible set holds its key
+ * (bf16 under FOCUS_MASK_CT, float32 under both masks; bf16 under
+ * FOCUS_MASK_KMER_LOCAL it may reach other rows of the key's 32-row tiles).
  */
 typedef struct {
   focus_layout_totals totals;

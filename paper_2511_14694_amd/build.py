@@ -33,12 +33,13 @@ HIPCC_FLAGS = [
 ]
 
 
-# Per-source extra flags.  The attention kernels never see a NaN (finite
-# inputs; masked scores are -inf), so their max reductions need no NaN
-# canonicalisation (device code only: the host checks test for NaN).  Their
-# compiler-visible MFMAs (scores) write VGPRs, which the softmax reads directly:
-# attn_ct keeps its output accumulators in AGPRs by itself, and by default the
-# compiler would put every MFMA result of so large a kernel there.
+# Per-source extra flags.  The attention kernels' max reductions need no NaN
+# canonicalisation (masked scores are -inf; a row with a NaN score is NaN whichever
+# operand a maximum keeps; infinities and NaNs of V are told by their bits).  Device
+# code only: the host checks test for NaN.  Their compiler-visible MFMAs (scores)
+# write VGPRs, which the softmax reads directly: attn_ct keeps its output
+# accumulators in AGPRs by itself, and by default the compiler would put every MFMA
+# result of so large a kernel there.
 EXTRA_FLAGS = {"window_attn.hip": ["-Xarch_device", "-fno-honor-nans", "-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 

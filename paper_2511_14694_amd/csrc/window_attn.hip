@@ -1228,6 +1228,43 @@ __global__ __launch_bounds__(256, 1) void attn_ct(
   // cache row 32 J + r - pad while J < 2 nct, then window row 32 (J - 2 nct) + r.
   const int J0 = 2 * tb;
 
+  // Infinities and NaNs in V.  Every row of the block sees every key before window
+  // row q0, but a key of its own rows (the band: local tiles band0 on) is also
+  // multiplied with the zero probability of the rows before it, and zero times an
+  // infinity is a NaN.  So each wave looks through its part of the band's V tiles
+  // once they are in LDS, before the barrier that hands them to the others, and
+  // clears what is not finite; if any wave did, the rows that see such a key get
+  // its value at the end.
+  __shared__ int vfound[C::kWaves];
+  const int band0 = nct + q0 / C::kBK - tb;
+  // clears this wave's part of local tile t, which has landed; true if it had to
+  auto clear_v = [&](int t) __attribute__((always_inline)) {
+    if (t < band0 || t >= ntiles) return false;
+    typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+    typedef __attribute__((address_space(3))) u32x4 lds_u4;
+    lds_u4* p = (lds_u4*)(uintptr_t)(ldsw + (4 + (t & 3)) * C::kTile + lane * 16);
+    u32x4 w[C::kDma];
+    u16x2 mx = {0, 0};  // largest magnitude of the 16-bit halves: from 0x7f80 on not finite
+#pragma unroll
+    for (int i = 0; i < C::kDma; ++i) w[i] = p[i * 64];
+#pragma unroll
+    for (int i = 0; i < C::kDma; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        mx = __builtin_elementwise_max(mx, __builtin_bit_cast(u16x2, w[i][e] & 0x7fff7fffu));
+    if (!__builtin_expect(__any(max(mx[0], mx[1]) >= 0x7f80), 0)) return false;
+#pragma unroll
+    for (int i = 0; i < C::kDma; ++i) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        if ((w[i][e] & 0x7f80u) == 0x7f80u) w[i][e] &= 0xffff0000u;
+        if ((w[i][e] & 0x7f800000u) == 0x7f800000u) w[i][e] &= 0xffffu;
+      }
+      p[i * 64] = w[i];
+    }
+    return true;
+  };
+
   // LDS operand addresses (lane parts; stages and sub-tile rows are immediates).
   // K row 32 half + l32, chunk 2 s + g sits at chunk (2 s + g) ^ (l32 mod kCh16).
   uint32_t kofs[C::kKsteps];
@@ -1427,14 +1464,19 @@ __global__ __launch_bounds__(256, 1) void attn_ct(
     });
   };
 
-  // vmcnt(n): this wave's copies older than its last n have landed
-  auto wait_copies = [&](bool keep_one_step) __attribute__((always_inline)) {
+  // vmcnt(n): this wave's copies older than its last n have landed, those of local
+  // tile t among them
+  auto wait_copies = [&](bool keep_one_step, int t) __attribute__((always_inline)) {
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
     constexpr int kVm = C::kPerStep;
     if (keep_one_step)
       __builtin_amdgcn_s_waitcnt((kVm & 15) | ((kVm >> 4) << 14) | (7 << 4) | (15 << 8));
     else
       __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));  // vmcnt(0)
+    if (clear_v(t)) {
+      if (lane == 0) vfound[wave] = 1;
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    }
     __builtin_amdgcn_s_barrier();
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
     __builtin_amdgcn_sched_barrier(0);
@@ -1464,7 +1506,7 @@ __global__ __launch_bounds__(256, 1) void attn_ct(
     advance_v(st);
     phase_b(mask_none(), 2 * u + 1, 1, 0);
     // step u + 1 reads K of tile u + 2: wait for it (tile u + 3 may stay in flight)
-    wait_copies(true);
+    wait_copies(true, u + 2);
   };
   auto step = [&](int u, auto mask_c) __attribute__((always_inline)) {
     if (u + 3 < ntiles) {
@@ -1477,7 +1519,7 @@ __global__ __launch_bounds__(256, 1) void attn_ct(
     phase_a(mask_c, 2 * u + 1, nullptr, 0, c_0());
     advance_v(u & 3);
     phase_b(mask_c, 2 * u + 1, 1, 0);
-    wait_copies(u + 3 < ntiles);
+    wait_copies(u + 3 < ntiles, u + 2);
   };
 
   // The scale arrives by a scalar load whose first use is inside the loop;
@@ -1510,6 +1552,11 @@ __global__ __launch_bounds__(256, 1) void attn_ct(
         for (int s = 0; s < C::kKsteps; ++s) asm volatile("" : "+v"(qf[i][s]));
     }
   }
+  {
+    const bool found = clear_v(0) | clear_v(1);
+    if (lane == 0) vfound[wave] = found;
+  }
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   __atomic_signal_fence(__ATOMIC_SEQ_CST);
   __builtin_amdgcn_s_barrier();
   __atomic_signal_fence(__ATOMIC_SEQ_CST);
@@ -1517,7 +1564,7 @@ __global__ __launch_bounds__(256, 1) void attn_ct(
   if (wq[1] >= T) {
     for (int u = 0; u < ntiles; ++u) {
       if (u + 3 < ntiles) issue_tile(tile_src(u + 3), (u + 3) & 3);
-      wait_copies(u + 3 < ntiles);
+      wait_copies(u + 3 < ntiles, u + 2);
     }
     return;
   }
@@ -1544,6 +1591,60 @@ __global__ __launch_bounds__(256, 1) void attn_ct(
   for (; u < u1; ++u) clean_step(u);
   for (; u < ntiles; ++u) step(u, mask_hi());
 
+  // The values cleared from V: each row of this wave takes those of the keys up to
+  // it (of this workgroup's tiles) into its stored output, a lane D / 64 columns.
+  // A finite sum becomes the value; two that differ make a NaN.
+  auto add_cleared = [&]() __attribute__((always_inline)) {
+    constexpr int kE = D / 64;
+    auto bad = [](uint32_t a) { return (a & 0x7f80u) == 0x7f80u; };  // (bf16 bits)
+    auto join = [&](uint32_t a, uint32_t x) { return !bad(a) || a == x ? x : 0x7fc0u; };
+    __threadfence();  // (other lanes stored the outputs)
+    uint32_t cl[kE] = {};
+    for (int u = q0; u < nwk; u += 32) {
+      uint16_t x[32][kE];
+      const int t = nct + u / C::kBK - tb;
+#pragma unroll
+      for (int r = 0; r < 32; ++r) {
+        const uint16_t* vp =
+            reinterpret_cast<const uint16_t*>(vwin + (int64_t)min(u + r, nwk - 1) * row_bytes) + lane * kE;
+#pragma unroll
+        for (int e = 0; e < kE; ++e) x[r][e] = vp[e];
+      }
+#pragma unroll
+      for (int r = 0; r < 32; ++r)
+#pragma unroll
+        for (int e = 0; e < kE; ++e) {
+          if (t >= 0 && t < ntiles && bad(x[r][e])) cl[e] = join(cl[e], x[r][e]);
+          x[r][e] = (uint16_t)cl[e];
+        }
+      if (u != wq[0] && u != wq[1]) continue;
+      if (sp.n > 1) {
+        uint32_t* p = reinterpret_cast<uint32_t*>(sp.po + ((((int64_t)split * sp.nwl + li) * sp.rows + u) * H + h) * D) +
+                      lane * kE;
+#pragma unroll
+        for (int r = 0; r < 32; ++r)
+#pragma unroll
+          for (int e = 0; e < kE; ++e)
+            if (x[r][e] && u + r < min(T, (int)sp.rows)) {
+              uint32_t& o = p[(int64_t)r * H * D + e];
+              const bool fin = (o & 0x7f800000u) != 0x7f800000u;
+              o = fin ? (uint32_t)x[r][e] << 16 : join(o >> 16, x[r][e]) << 16;
+            }
+      } else {
+        uint16_t* p = reinterpret_cast<uint16_t*>(d.o) + ((tok0 + u) * H + h) * D + lane * kE;
+#pragma unroll
+        for (int r = 0; r < 32; ++r)
+#pragma unroll
+          for (int e = 0; e < kE; ++e)
+            if (x[r][e] && u + r < T) {
+              uint16_t& o = p[(int64_t)r * H * D + e];
+              o = (uint16_t)join(o, x[r][e]);
+            }
+      }
+    }
+  };
+  const bool clear = uniform(vfound[0] | vfound[1] | vfound[2] | vfound[3]) != 0;
+
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
     o_ready(i);
@@ -1566,7 +1667,10 @@ __global__ __launch_bounds__(256, 1) void attn_ct(
     }
     if (g == 0 && d.lse) d.lse[(tok0 + qi[i]) * H + h] = (m_run[i] + log2f(l_tot)) * kLn2;
   }
-  if (sp.n > 1) return;
+  if (sp.n > 1) {
+    if (__builtin_expect(clear, 0)) add_cleared();
+    return;
+  }
   // O through this wave's part of the (now free) stages, 16-byte chunk c of row r
   // at c ^ (r mod kCh16), so that a store writes whole rows: 8 bytes a lane of 32
   // rows each took 4.2 us of a workgroup's 45 at 100 kb.
@@ -1598,6 +1702,7 @@ __global__ __launch_bounds__(256, 1) void attn_ct(
     if (q < T)
       *reinterpret_cast<u32x4*>(reinterpret_cast<__bf16*>(d.o) + ((tok0 + q) * H + h) * D + 8 * c) = w;
   }
+  if (__builtin_expect(clear, 0)) add_cleared();
 }
 
 // --------------------------------------- bf16 MFMA, summary queries under C(t)

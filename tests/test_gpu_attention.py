@@ -392,6 +392,37 @@ def test_f32_infinite_value_stays_with_the_rows_that_see_it(D, mask):
     assert (o[ok] - want[ok]).abs().max().item() <= 2e-5
 
 
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("seq,W,k,H,Hkv", [
+    ([333], 333, 20, 2, 1),       # no cache: the first key tiles are the band; one workgroup per item
+    ([1500], 300, 30, 32, 8),     # partial and full cache tiles; one workgroup per item
+    ([3000], 1000, 10, 2, 1),     # key split in two
+    ([3000], 3000, 0, 2, 2),      # key split in five, ranges that start inside a band
+])
+def test_bf16_infinite_value_stays_with_the_rows_that_see_it(seq, W, k, H, Hkv, D):
+    """A value of V that is not finite reaches the rows whose visible set holds
+    its key and no other (probability 0 times it would be NaN), wherever its row
+    lies in the 32-row blocks and 256-row tiles; everything else is bit-identical."""
+    announce(f"attn bf16 infinite V seq={seq} W={W} k={k} H={H}/{Hkv} D={D}")
+    p = Prefill(seq, W, np.full(-(-seq[0] // W), k, np.int32), H, Hkv, D, "bf16", seed=66)
+    off, ntok = (p.lay[n].cpu().tolist() for n in ("win_tok_off", "win_ntok"))
+    inf, nan, head, col = float("inf"), float("nan"), Hkv - 1, D // 2 + 1
+    heads = slice(head * (H // Hkv), (head + 1) * (H // Hkv))
+    rows = [0, 1, 31, 32, 47, 63, 64, 95, 96, 160, 255, 256, 290]
+    for w in (0, len(off) - 1):
+        o0, T = off[w], ntok[w]
+        for bad in [[(t, (inf, -inf, nan)[t % 3])] for t in rows + [T - 1] if t < T] + [[(40, inf), (41, -inf), (200, inf)]]:
+            keep = p.v.clone()
+            want = p.o.clone()
+            for t, x in bad:
+                p.v[o0 + t, head, col] = x
+                want[o0 + t:o0 + T, heads, col] += x   # (finite + x = x, inf - inf = NaN)
+            o, lse = p.attn()
+            p.v = keep
+            assert torch.equal(lse, p.lse), bad
+            assert torch.equal(torch.nan_to_num(o, nan=7e30), torch.nan_to_num(want, nan=7e30)), (w, bad)
+
+
 @pytest.mark.parametrize("L,W,kmer,D", [(16, 16, 0, 64), (17, 17, 0, 128), (129, 64, 63, 64), (1, 1, 1, 128), (531, 33, 4, 64)])
 def test_f32_tile_edges(L, W, kmer, D):
     """float32 windows on and around the 16-row query tile and the key blocks
