@@ -1004,7 +1004,10 @@ __device__ __forceinline__ float row_max(const f32x16& s) {
 // the instructions is the whole schedule: the phases are written out MFMA by
 // MFMA with the vector instructions, reads and copies dealt between them.  A
 // barrier closes every 64-key step; at its end each wave waits only for the
-// copies of the tile the next step starts reading.
+// copies of the tile the next step starts reading.  From the tile on that block 1's
+// rows no longer reach (it lies past their diagonal, or the window ends before
+// block 0's rows and block 0 took them over) block 0 goes on alone in loops of its own
+// (solo_step), and where it is past its diagonal too the wave only copies.
 //
 // What bounds it: the chip's power limit and, with one wave per SIMD, issue slots
 // (a phase of 16 MFMAs has 102 instructions, 61 of them vector; the MFMA pipe is
@@ -1017,7 +1020,12 @@ __device__ __forceinline__ float row_max(const f32x16& s) {
 // A persistent form (one workgroup per compute unit over many items, the next
 // item's first tiles and Q on their way during the last steps) was slower: 1 Mb
 // 81.8 ms, 100 kb 2.25; so were branches around dead sub-tiles in the masked steps
-// (the accumulators of the two sides met in different registers: 500 spills).
+// (the accumulators of the two sides met in different registers: 500 spills).  The
+// solo loops have none: with every sub-tile computed for both blocks -> with them,
+// windows of 1 000 at 4 kb 72 -> 67 us, 32 kb 584 -> 562, 128 kb 3.04 -> 2.94 ms,
+// windows of 512 at 128 kb 4.84 -> 4.63, windows of 64 at 20 kb 966 -> 835 us (the
+// eight waves: 69, 590, 3.14, 5.58, 868).  Looking for infinities in the band's V
+// tiles is in all of these but the last and takes 1 to 4 % (most at 4 kb).
 template <int D>
 struct CtCfg {
   static constexpr int kWaves = 4;
@@ -1144,8 +1152,10 @@ __global__ __launch_bounds__(256, 1) void attn_ct(
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l32 = lane & 31, g = lane >> 5;
   // A wave's query blocks: rows q0 + 32 (7 - wave) and q0 + 32 wave, so that
   // the longer of every wave's two is well above the first diagonal tile (see
-  // the clean steps below).
-  const int wq[2] = {q0 + 32 * (2 * C::kWaves - 1 - wave), q0 + 32 * wave};
+  // the clean steps below).  Near the window's end, where only the second has
+  // rows, it is block 0 (the one the solo steps compute).
+  const int wq_hi = q0 + 32 * (2 * C::kWaves - 1 - wave), wq_lo = q0 + 32 * wave;
+  const int wq[2] = {wq_hi < T ? wq_hi : wq_lo, wq_hi < T ? wq_lo : wq_hi};
   const int qi[2] = {wq[0] + l32, wq[1] + l32};
 
   // Q^T as the B operand: lane holds query l32, head_dim [16 s + 8 g, +8).
@@ -1323,10 +1333,10 @@ __global__ __launch_bounds__(256, 1) void attn_ct(
       for (int v = 0; v < 16; ++v) sacc[i][v] = 0.f;
     sacc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kop[s], qf[i][s], sacc[i], 0, 0, 0);
   };
-  auto mfma_o = [&](int i, int x) __attribute__((always_inline)) {
+  auto mfma_o = [&](int i, int x, int ip) __attribute__((always_inline)) {
     asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0"
                  : "+a"(oacc[i][x % C::kDtiles])
-                 : "v"(vop[x]), "v"(pb[i][x / C::kDtiles]));
+                 : "v"(vop[x]), "v"(pb[ip][x / C::kDtiles]));
   };
   auto o_ready = [&](int i) __attribute__((always_inline)) {
 #pragma unroll
@@ -1360,9 +1370,9 @@ __global__ __launch_bounds__(256, 1) void attn_ct(
     if (M == 2) x = kk < mk.lo ? -INFINITY : x;
     return x;
   };
-  // The probabilities of block i's scores against its running reference, and
-  // their sum over the lane's 16 keys.
-  auto probs = [&](auto mode, int i, const Mask& mk) __attribute__((always_inline)) {
+  // The probabilities of block i's scores against its running reference (to
+  // pb[ip]), and their sum over the lane's 16 keys.
+  auto probs = [&](auto mode, int i, int ip, const Mask& mk) __attribute__((always_inline)) {
     float psum = 0.f;
 #pragma unroll
     for (int v = 0; v < 16; v += 2) {
@@ -1370,14 +1380,14 @@ __global__ __launch_bounds__(256, 1) void attn_ct(
       const float p1 = __builtin_amdgcn_exp2f(fmaf(score(mode, i, v + 1, mk), sc, -m_run[i]));
       psum += p0;
       psum += p1;
-      pb[i][v >> 3][(v >> 1) & 3] = focus::pack_bf16x2(p0, p1);
+      pb[ip][v >> 3][(v >> 1) & 3] = focus::pack_bf16x2(p0, p1);
     }
     return psum;
   };
   // The sum, which the row sum needs anyway, says whether the reference is still
   // high enough (numerator and denominator use the same one, so any is exact).
   // If not: the row's maximum, the accumulator rescaled, the probabilities again.
-  auto settle = [&](auto mode, int i, float psum, bool big, const Mask& mk) __attribute__((always_inline)) {
+  auto settle = [&](auto mode, int i, int ip, float psum, bool big, const Mask& mk) __attribute__((always_inline)) {
     if (__builtin_expect(big, 0)) {
       f32x16 s;
 #pragma unroll
@@ -1392,7 +1402,7 @@ __global__ __launch_bounds__(256, 1) void attn_ct(
         for (int v = 0; v < 16; ++v) oacc[i][dt][v] *= alpha;
       o_ready(i);
       m_run[i] = m_new;
-      psum = probs(mode, i, mk);
+      psum = probs(mode, i, ip, mk);
     }
     l_run[i] += psum;
   };
@@ -1422,7 +1432,7 @@ __global__ __launch_bounds__(256, 1) void attn_ct(
       if (c < C::kKsteps)
         mfma_s(i, c);
       else
-        mfma_o(i, c - C::kKsteps);
+        mfma_o(i, c - C::kKsteps, i);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int v = 0; v < 16; ++v)
@@ -1443,7 +1453,48 @@ __global__ __launch_bounds__(256, 1) void attn_ct(
       rest(c);
       __builtin_amdgcn_sched_barrier(0);
     }
-    settle(mask_c, o, psum, big, mk);
+    settle(mask_c, o, o, psum, big, mk);
+  };
+  // The same for block 0 alone (block 1 has no row that sees a key from here on):
+  // its score products of sub-tile j + 1, then its output products of sub-tile j,
+  // and between those the softmax of sub-tile j + 1.  pb[j & 1] (ip) holds sub-tile
+  // j's probabilities.
+  auto solo_phase = [&](auto mask_c, int j, const int ip, const int hk2, const int hv) __attribute__((always_inline)) {
+    constexpr int N = C::kMfma, S = C::kKsteps, O = N - S;
+    float pr[16], psum = 0.f;
+    bool big = false;
+    const Mask mk = mask_of(0, j + 1);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int c = 0; c < S; ++c) {
+      mfma_s(0, c);
+      __builtin_amdgcn_sched_barrier(0);
+      read_k(hk2, c);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int c = 0; c < O; ++c) {
+      mfma_o(0, c, ip);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int v = 0; v < 16; ++v)
+        if (v >= ct_exps(c - 1, O) && v < ct_exps(c, O))
+          pr[v] = __builtin_amdgcn_exp2f(fmaf(score(mask_c, 0, v, mk), sc, -m_run[0]));
+#pragma unroll
+      for (int v = 0; v < 16; ++v)
+        if (v >= ct_exps(c - 2, O) && v < ct_exps(c - 1, O)) {
+          psum += pr[v];
+          if (v & 1) {
+            uint32_t w = focus::pack_bf16x2(pr[v - 1], pr[v]);
+            asm volatile("" : "+v"(w));
+            pb[1 - ip][v >> 3][(v >> 1) & 3] = w;
+          }
+        }
+      if (c == O - 1) big = __any(psum > kLazySum);
+      read_v(hv, c);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    settle(mask_c, 0, 1 - ip, psum, big, mk);
   };
   // Phase A of sub-tile j (the half K0 of src's copies, K or V, go to stage cst) ...
   auto phase_a = [&](auto mask_c, int j, const Src* src, int cst, auto k0_c) __attribute__((always_inline)) {
@@ -1522,6 +1573,15 @@ __global__ __launch_bounds__(256, 1) void attn_ct(
     wait_copies(u + 3 < ntiles, u + 2);
   };
 
+  auto solo_step = [&](int u, auto mask_c) __attribute__((always_inline)) {
+    if (u + 3 < ntiles) issue_tile(tile_src(u + 3), (u + 3) & 3);
+    advance_k(u & 3);
+    solo_phase(mask_c, 2 * u, 0, 0, 1);
+    advance_v(u & 3);
+    solo_phase(mask_c, 2 * u + 1, 1, 1, 0);
+    wait_copies(u + 3 < ntiles, u + 2);
+  };
+
   // The scale arrives by a scalar load whose first use is inside the loop;
   // using it here puts the wait for that load before the loop instead of
   // (conservatively) at the top of every iteration.
@@ -1560,12 +1620,16 @@ __global__ __launch_bounds__(256, 1) void attn_ct(
   __atomic_signal_fence(__ATOMIC_SEQ_CST);
   __builtin_amdgcn_s_barrier();
   __atomic_signal_fence(__ATOMIC_SEQ_CST);
-  // A wave whose rows all lie past the window's end only copies.
-  if (wq[1] >= T) {
-    for (int u = 0; u < ntiles; ++u) {
+  // Steps that only copy: the rest of the tiles, from u on.
+  auto copy_rest = [&](int u) __attribute__((always_inline)) {
+    for (; u < ntiles; ++u) {
       if (u + 3 < ntiles) issue_tile(tile_src(u + 3), (u + 3) & 3);
       wait_copies(u + 3 < ntiles, u + 2);
     }
+  };
+  // A wave whose rows all lie past the window's end does nothing else.
+  if (wq[0] >= T) {
+    copy_rest(0);
     return;
   }
 #pragma unroll
@@ -1581,15 +1645,24 @@ __global__ __launch_bounds__(256, 1) void attn_ct(
   // (the output accumulators are still zero: nothing to rescale)
   first_max(mask_lo_hi(), 0, mask_of(0, 0));
   first_max(mask_lo_hi(), 1, mask_of(1, 0));
-  l_run[0] = probs(mask_lo_hi(), 0, mask_of(0, 0));
+  l_run[0] = probs(mask_lo_hi(), 0, 0, mask_of(0, 0));
   // Let every scalar load land before the loop (lgkmcnt(0) once): a scalar
   // load still pending there would make the compiler wait for all LDS reads
   // at every counter wait inside the loop.
   __builtin_amdgcn_s_waitcnt(0xC07F);
+  // Block i's rows see a key of the tiles below nl[i].
+  int nl[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) nl[i] = wq[i] < T ? max(0, min(nct + wq[i] / C::kBK + 1 - tb, ntiles)) : 0;
   int u = 0;
-  if (u0 > 0) step(u++, mask_lo_hi());
-  for (; u < u1; ++u) clean_step(u);
-  for (; u < ntiles; ++u) step(u, mask_hi());
+  if (nl[1] > 0) {
+    if (u0 > 0) step(u++, mask_lo_hi());
+    for (; u < u1; ++u) clean_step(u);
+    for (; u < nl[1]; ++u) step(u, mask_hi());
+  }
+  if (u < u0 && nl[0] > 0) solo_step(u++, mask_lo_hi());
+  for (; u < nl[0]; ++u) solo_step(u, mask_hi());
+  copy_rest(u);
 
   // The values cleared from V: each row of this wave takes those of the keys up to
   // it (of this workgroup's tiles) into its stored output, a lane D / 64 columns.

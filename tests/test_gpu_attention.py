@@ -451,3 +451,17 @@ def test_ct_query_and_key_tile_edges(W, k, seq, D):
     ref = build_layout(seq, W, km)
     p = Prefill(seq, W, km, 8, 4, D, "bf16", seed=65)
     compare_windows(ref, p, range(ref["n_windows"]), [0, 3, 7], "ct tile edges")
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("W,k,n", [(16, 4, 40), (64, 16, 17), (100, 29, 18), (150, 10, 5), (200, 9, 6), (384, 3, 3)])
+def test_ct_blocks_computed_alone(W, k, n, D):
+    """Windows that end inside a query tile, so that waves have rows in one of
+    their two blocks or in none, behind caches of many lengths (the first key tile
+    masked by 4 to 60 rows, in steps of 4, among them)."""
+    announce(f"attn ct blocks alone W={W} k={k} n={n} D={D}")
+    seq = [W * n - 3, W]
+    km = np.full(n + 1, k, np.int32)
+    ref = build_layout(seq, W, km)
+    p = Prefill(seq, W, km, 8, 4, D, "bf16", seed=67)
+    compare_windows(ref, p, range(ref["n_windows"]), [0, 3, 7], "ct blocks alone")
