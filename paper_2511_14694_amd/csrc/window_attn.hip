@@ -2248,9 +2248,12 @@ __global__ __launch_bounds__(256) void attn_combine(focus_attn_desc d, Split sp)
 //   O^T = V^T P^T  the scores of a lane are keys 4 g + r of query l % 16; k-step
 //                  r takes those keys, and output block 4 f + c is head_dim
 //                  64 f + 4 row + c, so V and O move 16 bytes a lane.
-// 4 kb, one head of 64: 248 us with 4 lanes per query row and one key at a time
-// on the vector unit, 30 us now; 16 kb, 4 heads of 128 run at 60 TFLOP/s
-// (0.36 ms).  8 waves per workgroup: the same for one head, 0.46 ms for four.
+// 4 kb, one head of 64: 247 us with 4 lanes per query row and one key at a time
+// on the vector unit, 29 us now; 16 kb, 4 heads of 128: 701 -> 304 us.  8 waves
+// per workgroup: the same for one head, a quarter longer for four.  Error against
+// float64 (8 kb, 2 heads of 128, windows of 512): 3.5e-7 on the vector unit, 3.7e-7
+// with one accumulator for a score, 2.1e-7 with four (299 us with one for the four
+// heads above).
 template <int D, bool KL>
 __global__ __launch_bounds__(64 * kF32Waves, D == 64 ? 2 : 1) void attn_f32(focus_attn_desc d, float sc, int64_t n_pairs, int QT) {
   constexpr int kT = 128 / D;              // 16-key tiles per block
@@ -2338,15 +2341,25 @@ __global__ __launch_bounds__(64 * kF32Waves, D == 64 ? 2 : 1) void attn_f32(focu
   float m = kMinit, l = 0.f;  // m: of the row; l: of this lane's keys
   auto compute = [&](int jb, const Block& x) __attribute__((always_inline)) {
     const int j0 = 16 * kT * jb;
-    f32x4 s[kT];
+    // (accumulators of 32 products each, added at the end: shorter sums, less rounding)
+    constexpr int kA = kI / 2;
+    f32x4 sa[kT][kA], s[kT];
 #pragma unroll
-    for (int t = 0; t < kT; ++t) s[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int t = 0; t < kT; ++t)
+#pragma unroll
+      for (int a = 0; a < kA; ++a) sa[t][a] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int i = 0; i < kI; ++i)
 #pragma unroll
       for (int c = 0; c < 4; ++c)
 #pragma unroll
-        for (int t = 0; t < kT; ++t) s[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(x.k[t][i][c], qv[i][c], s[t], 0, 0, 0);
+        for (int t = 0; t < kT; ++t)
+          sa[t][i % kA] = __builtin_amdgcn_mfma_f32_16x16x4f32(x.k[t][i][c], qv[i][c], sa[t][i % kA], 0, 0, 0);
+#pragma unroll
+    for (int t = 0; t < kT; ++t) {
+      s[t] = sa[t][0] + sa[t][1];
+      if constexpr (kA == 4) s[t] += sa[t][2] + sa[t][3];
+    }
     const bool masked = KL || j0 + 16 * kT - 1 > Cw + q0;
     bool any = true;
     uint32_t vmax = 0;  // largest exponent field of the block's V (all ones: an infinity or NaN)

@@ -435,6 +435,20 @@ def test_f32_tile_edges(L, W, kmer, D):
 
 
 @pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("L,W,k,H", [(3339, 1000, 500, 2), (8000, 512, 100, 2)])
+def test_f32_error_of_a_score_is_that_of_32_products(L, W, k, H, D):
+    """Relative L2 error of the whole float32 output: scores are sums of 32 products
+    at a time (a sum of 128 rounds about twice as much), which leaves 2.3e-7 at most
+    here; one accumulator over head_dim 128 left 3.4e-7 and more."""
+    announce(f"attn f32 error L={L} W={W} k={k} H={H} D={D}")
+    km = np.full(-(-L // W), k, np.int32)
+    ref = build_layout([L], W, km)
+    p = Prefill([L], W, km, H, H, D, "f32", seed=69)
+    o, _ = A.prefill_sequential(ref, to64(p.q), to64(p.k), to64(p.v))
+    assert np.linalg.norm(to64(p.o) - o) <= 2.8e-7 * np.linalg.norm(o)
+
+
+@pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("W,k,seq", [
     (40, 8, [400]),          # one 45-row query tile: three waves of the tile without a row
     (255, 300, [1020]),      # exactly one query tile of 256 rows
