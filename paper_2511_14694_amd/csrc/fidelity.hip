@@ -486,24 +486,25 @@ __global__ __launch_bounds__(kThreads) void fid_logits_half(focus_fidelity_desc 
 // metrics every element of a thread's float4 belongs to one metric for the
 // whole run.  One workgroup reads only about 50 GB/s, so with a workspace a
 // sequence is split over up to kMaxMeanSplits workgroups (fid_mean_part), whose
-// sums fid_mean_merge adds; without one, or for short sequences, fid_seq_mean
-// takes a workgroup per sequence.  Eight sequences of 125 000 positions:
-// 220 us with one workgroup of 256 threads reading five floats each, 50 us with
-// one of 1024 as here, 14 us split (10 for the parts, 4 for the merge).
+// sums fid_mean_merge adds; without one fid_seq_mean takes a workgroup per sequence;
+// short sequences go to fid_short_mean.  Eight sequences of 125 000 positions:
+// 135 us with one workgroup of 256 threads reading five floats each, 50 us with one
+// of 1024 as here, 10 us split.
 constexpr int kMaxMeanSplits = 64;
 constexpr int kMeanPerSplit = 1024;  // positions a split is worth
 
-// sum[m] of this thread over out[f0 .. f1) (floats of whole rows)
+// sum[m] of thread tid over out[f0 .. f1) (floats of whole rows); LANES threads
+// take the 16-byte-aligned part, four more the floats before and after it
 template <int LANES>
-__device__ inline void sum_rows(const float* out, int64_t f0, int64_t f1, float (&sum)[FOCUS_FID_N]) {
+__device__ inline void sum_rows(const float* out, int64_t f0, int64_t f1, int tid, float (&sum)[FOCUS_FID_N]) {
   constexpr int kUnroll = 8;
   static_assert(4 * LANES % FOCUS_FID_N == 0, "a fixed metric per element");
-  const int tid = threadIdx.x;
 #pragma unroll
   for (int m = 0; m < FOCUS_FID_N; ++m) sum[m] = 0.f;
   // [a0, a0 + 4 nv) is the 16-byte-aligned part
   const int64_t skew = (int64_t)((reinterpret_cast<uintptr_t>(out + f0) >> 2) & 3);
   const int64_t a0 = min(f0 + ((4 - skew) & 3), f1), nv = (f1 - a0) / 4;
+  const int head = (int)(a0 - f0), edge = (int)(f1 - f0 - 4 * nv);
   const float4* v = reinterpret_cast<const float4*>(out + a0);
   if (tid < LANES) {
     float acc[4] = {0.f, 0.f, 0.f, 0.f};
@@ -524,15 +525,15 @@ __device__ inline void sum_rows(const float* out, int64_t f0, int64_t f1, float 
     for (int j = 0; j < 4; ++j)
 #pragma unroll
       for (int m = 0; m < FOCUS_FID_N; ++m)
-        if ((a0 + 4 * tid + j) % FOCUS_FID_N == m) sum[m] = acc[j];
-  } else if (tid == LANES) {
-    // the floats before and after the aligned part
-    const int64_t head = a0 - f0, edge = f1 - f0 - 4 * nv;
-    for (int64_t i = 0; i < edge; ++i) {
-      const int64_t f = i < head ? f0 + i : a0 + 4 * nv + (i - head);
+        if ((head + 4 * tid + j) % FOCUS_FID_N == m) sum[m] = acc[j];
+  } else if (tid < LANES + 4) {
+    for (int i = tid - LANES; i < edge; i += 4) {
+      // (f1 and f0 are whole rows: the metric is counted from the nearer)
+      const int c = i < head ? i : (int)(FOCUS_FID_N - edge + i) % FOCUS_FID_N;
+      const float x = i < head ? out[f0 + i] : out[f1 - edge + i];
 #pragma unroll
       for (int m = 0; m < FOCUS_FID_N; ++m)
-        if (f % FOCUS_FID_N == m) sum[m] += out[f];
+        if (c == m) sum[m] += x;
     }
   }
 }
@@ -572,9 +573,45 @@ __global__ __launch_bounds__(kMeanThreads) void fid_seq_mean(focus_fidelity_desc
     if (tid == 0) focus::raise_err(d.err, FOCUS_ERR_BOUNDS);
   }
   float sum[FOCUS_FID_N];
-  sum_rows<kMeanLanes>(d.out, t0 * FOCUS_FID_N, t1 * FOCUS_FID_N, sum);
+  sum_rows<kMeanLanes>(d.out, t0 * FOCUS_FID_N, t1 * FOCUS_FID_N, tid, sum);
   const float x = block_sums<kMeanThreads>(sum);
   if (tid < FOCUS_FID_N) d.seq_mean[(int64_t)b * FOCUS_FID_N + tid] = t1 > t0 ? x / (float)(t1 - t0) : 0.f;
+}
+
+// Short sequences (not worth a split on average): per (1 or 4) to a workgroup of
+// four waves, a wave each; one longer than alone positions the workgroup takes
+// together.  Bound by what a workgroup costs to start and by one round of loads.
+// 20 000 sequences of 50 positions: 22 us with a workgroup of 256 and a tree sum in
+// LDS, 122 with one of 1024 each (fid_seq_mean), 22 here; 4 000 of 250: 7.5, 29,
+// 7.9; 100 of 1000: 4.1, 4.7, 3.9; one of 400 000 among 4 000 of 25: 421, 108, 132.
+constexpr int kShortWaves = 4;
+__global__ __launch_bounds__(64 * kShortWaves) void fid_short_mean(focus_fidelity_desc d, int per, int alone) {
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int64_t b0 = (int64_t)blockIdx.x * per;
+  for (int s = 0; s < per && b0 + s < d.n_seq; ++s) {
+    int64_t t0, t1;
+    if (!seq_range(d, (int)(b0 + s), t0, t1) || t1 - t0 <= alone) continue;
+    float sum[FOCUS_FID_N];
+    sum_rows<250>(d.out, t0 * FOCUS_FID_N, t1 * FOCUS_FID_N, tid, sum);
+    __syncthreads();  // (the sums of the one before have been read)
+    const float x = block_sums<64 * kShortWaves>(sum);
+    if (tid < FOCUS_FID_N) d.seq_mean[(b0 + s) * FOCUS_FID_N + tid] = x / (float)(t1 - t0);
+  }
+  const int64_t b = b0 + wave;
+  if (wave >= per || b >= d.n_seq) return;
+  int64_t t0, t1;
+  if (!seq_range(d, (int)b, t0, t1)) {
+    t0 = t1 = 0;
+    if (lane == 0) focus::raise_err(d.err, FOCUS_ERR_BOUNDS);
+  }
+  if (t1 - t0 > alone) return;
+  float sum[FOCUS_FID_N];
+  sum_rows<60>(d.out, t0 * FOCUS_FID_N, t1 * FOCUS_FID_N, lane, sum);
+#pragma unroll
+  for (int m = 0; m < FOCUS_FID_N; ++m) {
+    const float x = wave_sum(sum[m]);
+    if (lane == 0) d.seq_mean[b * FOCUS_FID_N + m] = t1 > t0 ? x / (float)(t1 - t0) : 0.f;
+  }
 }
 
 // Split s of sequence b: its share of the positions, summed into
@@ -589,7 +626,7 @@ __global__ __launch_bounds__(kPartThreads) void fid_mean_part(focus_fidelity_des
   }
   const int64_t n = t1 - t0, u0 = t0 + n * s / n_split, u1 = t0 + n * (s + 1) / n_split;
   float sum[FOCUS_FID_N];
-  sum_rows<kPartLanes>(d.out, u0 * FOCUS_FID_N, u1 * FOCUS_FID_N, sum);
+  sum_rows<kPartLanes>(d.out, u0 * FOCUS_FID_N, u1 * FOCUS_FID_N, tid, sum);
   const float x = block_sums<kPartThreads>(sum);
   if (tid < FOCUS_FID_N) ws[(int64_t)blockIdx.x * FOCUS_FID_N + tid] = x;
 }
@@ -701,7 +738,17 @@ extern "C" focus_status focus_fidelity_ws(const focus_fidelity_desc* d, void* wo
       hipLaunchKernelGGL(fid_mean_merge, dim3(d->n_seq), dim3(64), 0, s, *d, ns, ws);
       return focus::launch_status();
     }
-    hipLaunchKernelGGL(fid_seq_mean, dim3(d->n_seq), dim3(kMeanThreads), 0, s, *d);
+    if (ns > 1) {
+      hipLaunchKernelGGL(fid_seq_mean, dim3(d->n_seq), dim3(kMeanThreads), 0, s, *d);
+    } else {
+      // (few sequences: a workgroup each, whose waves share one round of loads
+      // beyond what one wave takes in one; many: the workgroups' number counts.
+      // 1000 of 1000 positions: 6.8 us with one to a workgroup, 7.3 with four;
+      // 20 000 of 50: about 30 with one, 22 with four)
+      const int per = d->n_seq < 2048 ? 1 : kShortWaves;
+      hipLaunchKernelGGL(fid_short_mean, dim3((uint32_t)focus::ceil_div(d->n_seq, per)), dim3(64 * kShortWaves), 0, s,
+                         *d, per, per == 1 ? 384 : 1024);
+    }
     return focus::launch_status();
   }
   return FOCUS_OK;

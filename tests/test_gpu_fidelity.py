@@ -122,6 +122,26 @@ def test_sequence_means_split(cu):
         np.testing.assert_allclose(got.cpu().numpy(), ref, rtol=2e-6, atol=1e-9)
 
 
+@pytest.mark.parametrize("more", [0, 2100])
+def test_sequence_means_short(more):
+    """Many short sequences (one to a workgroup, or four): empty ones, one
+    position, around a wave's round of loads (384 positions) and the lengths from
+    which a workgroup takes a sequence together (385, 1025), next to one another
+    and at the end; sequences start at every 16-byte phase of the output rows.
+    Against the float64 mean of the device's own rows (sums of n float32: n 2^-24)."""
+    announce(f"fidelity short means, {more} more")
+    lens = [0, 1, 2, 3, 5, 47, 48, 49, 383, 384, 385, 1023, 1024, 1025, 5000, 1026, 2, 7]
+    lens += list(range(40)) + [9] * more + [3000]
+    cu = np.concatenate([[1], 1 + np.cumsum(lens)])
+    n = int(cu[-1]) + 1
+    assert {int(c) * 5 % 4 for c in cu} == {0, 1, 2, 3} and n // len(lens) < 1024
+    p, q = fw.fidelity_logits(n, 4, "f32", seed=n, device=DEV)
+    out, mean = F.focus_fidelity(p, q, cu_pos=cu)
+    torch.cuda.synchronize()
+    ref = FD.sequence_means(out.cpu().numpy().astype(np.float64), cu)
+    np.testing.assert_allclose(mean.cpu().numpy(), ref, rtol=2e-6, atol=1e-9)
+
+
 @pytest.mark.parametrize("name", list(fw.FIDELITY))
 def test_workload_full_size_sampled(name):
     n, vocab, dtype = fw.FIDELITY[name]
