@@ -418,22 +418,21 @@ constexpr int kStage2 = kATile2 + kBTile2;       // A then B
 // XCD x (blocks go to them round robin) takes a 4 x sbw / 2 part of each, so the
 // tiles it works on together share A stripes and B columns through its L2 while
 // all XCDs share the super block's in the last-level cache (101 000 x 4096 x
-// 4096: 2.83 -> 2.76 ms).
-__device__ inline bool wide_tile(int64_t bid, int64_t m_tiles, int64_t n_tiles, int sbw, int64_t& mt, int64_t& nt) {
+// 4096: 2.83 -> 2.76 ms).  A last group whose row stripes do not divide by four
+// goes without: the parts would be uneven and some XCDs without work.
+__device__ inline void wide_tile(int64_t bid, int64_t m_tiles, int64_t n_tiles, int sbw, int64_t& mt, int64_t& nt) {
   const int64_t per_group = (int64_t)kGroupM * n_tiles, grp0 = bid / per_group, in_grp = bid % per_group;
   const int rows = (int)min((int64_t)kGroupM, m_tiles - grp0 * kGroupM);
-  if (rows <= 0) return false;  // past the last group
-  if (sbw > 0) {
-    const int per = (rows + 3) / 4, sb = 4 * per * sbw;  // tiles of a super block, row stripes padded to 4 parts
+  if (sbw > 0 && rows % 4 == 0) {
+    const int per = rows / 4, sb = 4 * per * sbw;  // tiles of a super block
     const int r = (int)(in_grp % sb), x = r % focus::kXcds, i = r / focus::kXcds;
     const int mi = (x % 4) * per + i % per;
     mt = grp0 * kGroupM + mi;
     nt = in_grp / sb * sbw + (x / 4) * (sbw / 2) + i / per;
-    return mi < rows && nt < n_tiles;
+  } else {
+    mt = grp0 * kGroupM + in_grp % rows;
+    nt = in_grp / rows;
   }
-  mt = grp0 * kGroupM + in_grp % rows;
-  nt = in_grp / rows;
-  return nt < n_tiles;
 }
 
 template <class Epi>
@@ -442,7 +441,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_bf16_wide(focus_gemm_desc d,
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l32 = lane & 31,
             g = lane >> 5;
   int64_t mt, nt;
-  if (!wide_tile(blockIdx.x, m_tiles, d.n / kBN2, sbw, mt, nt)) return;
+  wide_tile(blockIdx.x, m_tiles, d.n / kBN2, sbw, mt, nt);
   const int64_t m0 = mt * kBM2, n0 = nt * kBN2;
   const int wm = (wave & 1) * 128, wn = (wave >> 1) * 128;  // this wave's 128 x 128 in the tile
 
@@ -691,7 +690,7 @@ focus_status launch_gemm(const focus_gemm_desc& d, const Epi& epi, focus_stream_
   const int64_t rounds = focus::ceil_div(m_tiles * n_tiles, cus), rounds2 = focus::ceil_div(m_tiles2 * n_tiles2, cus);
   if (d.n % kBN2 == 0 && 11 * rounds2 <= 4 * rounds) {
     const int sbw = super_block(n_tiles2);
-    const int64_t blocks = (sbw > 0 ? focus::ceil_div(m_tiles2, 4) * 4 : m_tiles2) * n_tiles2;
+    const int64_t blocks = m_tiles2 * n_tiles2;
     if (blocks > INT32_MAX) return FOCUS_E_SHAPE;
     hipLaunchKernelGGL(gemm_bf16_wide<Epi>, dim3((uint32_t)blocks), dim3(kThreads), 0, s, d, m_tiles2, sbw, epi);
   } else {

@@ -37,7 +37,8 @@ def test_gemm_matches_float64(m, n, k, out_dtype):
 
 @pytest.mark.parametrize("m,n,k", [(15, 128, 64), (16, 128, 576), (17, 256, 128), (32, 384, 64), (33, 128, 192),
                                    (65, 640, 64), (200, 12288, 128), (129, 16384, 64), (1025, 4224, 192),
-                                   (2100, 4096, 64), (2100, 4352, 192), (4000, 2560, 128)])
+                                   (2100, 4096, 64), (2100, 4352, 192), (4000, 2560, 128), (300, 32768, 192),
+                                   (2100, 4096, 192), (700, 6144, 192)])
 def test_gemm_kernel_edges(m, n, k):
     """Each kernel of the dispatch at its edges: row tiles of 16, 32 and 64 (one
     and several), fewer k-steps than waves, the 128 x 128 tile over several
