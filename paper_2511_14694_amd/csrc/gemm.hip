@@ -211,11 +211,12 @@ __device__ __forceinline__ void copy_to_lds(const void* src, uint32_t lds) {
 
 // Stores 64 x 64 results of one wave (get(i, j) = the f32x16 of its 32 x 32
 // block i, j: element v is row 8 (v / 4) + 4 g + v % 4, column l32) at C[row0 ..][col0 ..]
-// through kBlockLds floats of LDS of its own: the values are parked in rows of
+// through kBlockLds bytes of LDS of its own: the values are parked in rows of
 // kBlockRow floats (padded so that the two half-waves write different banks),
 // then eight lanes take a row, eight columns each, and store 16 bytes.
 // Same-wave LDS accesses complete in order, so no barrier is needed.
-template <int kBlockRow = 72, class Epi, class Get>
+constexpr int kBlockRow = 72, kBlockLds = 64 * kBlockRow * (int)sizeof(float);
+template <class Epi, class Get>
 __device__ __forceinline__ void store_block(float* ct, int lane, int64_t row0, int64_t col0, int64_t m, const Epi& epi,
                                             const typename Epi::Col8& cl, Get get) {
   const int l32 = lane & 31, g = lane >> 5;
@@ -238,9 +239,14 @@ __device__ __forceinline__ void store_block(float* ct, int lane, int64_t row0, i
   }
 }
 
-template <class Epi>
-__global__ __launch_bounds__(kThreads, 1) void gemm_bf16(focus_gemm_desc d, int64_t m_tiles, Epi epi) {
-  __shared__ __attribute__((aligned(1024))) char buf[kStages][kATile + kBTile];
+// NK > 0: K = 64 NK, all of it copied at once and waited for; a unit holds two
+// workgroups, so one's copies and stores overlap the other's products (with one
+// to two steps the four stages would only copy the last step again).
+template <class Epi, int NK = 0>
+__global__ __launch_bounds__(kThreads, NK > 0 ? 2 : 1) void gemm_bf16(focus_gemm_desc d, int64_t m_tiles, Epi epi) {
+  constexpr int kStage = kATile + kBTile;
+  constexpr int kLds = NK == 0 ? kStages * kStage : NK * kStage > 4 * kBlockLds ? NK * kStage : 4 * kBlockLds;
+  __shared__ __attribute__((aligned(1024))) char buf[kLds];
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l32 = lane & 31,
             g = lane >> 5;
   // Each XCD (blocks go to them round robin) takes a contiguous run of tiles,
@@ -279,10 +285,10 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_bf16(focus_gemm_desc d, int6
     b_src[i] = B + (int64_t)br * b_ld + n0 * 2 + (((pb >> 2) ^ (br & 3)) * 4 + (pb & 3)) * 16;
   }
   typedef const __attribute__((address_space(3))) char lds_char;
-  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_char*)&buf[0][0] + wave * 4 * 1024;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_char*)&buf[0] + wave * 4 * 1024;
   // copy c (of 8: A 0 .. 3, B 4 .. 7) of this wave for the step at k0 into a stage
   auto issue = [&](int64_t k0, int stage, int c) __attribute__((always_inline)) {
-    const uint32_t l = lds0 + stage * (kATile + kBTile);
+    const uint32_t l = lds0 + stage * kStage;
     if (c < 4)
       copy_to_lds(a_src[c] + k0 * 2, l + c * 1024);
     else
@@ -344,15 +350,6 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_bf16(focus_gemm_desc d, int6
     }
   };
 
-  // Step t, whose first half's operands are in registers: multiply them while
-  // the second half's are read; wait until those reads and step t + 1's copies
-  // have landed (the younger ones stay in flight) and barrier; multiply the
-  // second half while step t + 1's first half is read.  The copies of step t +
-  // 3 (past the end, of the last step again: every step starts the same
-  // number) go into the stage step t - 1 left, which every wave had read by
-  // that step's barrier.  One wave per SIMD: the matrix pipe works through the
-  // reads and the barrier.
-  const int64_t nk = d.k / kBKk;
   auto wait_barrier = [&](auto n) __attribute__((always_inline)) {
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
     constexpr int kVm = decltype(n)::value;  // vmcnt(kVm) expcnt(7) lgkmcnt(0)
@@ -361,30 +358,57 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_bf16(focus_gemm_desc d, int6
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
     __builtin_amdgcn_sched_barrier(0);
   };
+  if constexpr (NK > 0) {
 #pragma unroll
-  for (int u = 0; u < kStages - 1; ++u)
+    for (int t = 0; t < NK; ++t)
 #pragma unroll
-    for (int c = 0; c < kCopies; ++c) issue(min((int64_t)u, nk - 1) * kBKk, u, c);
-  wait_barrier(std::integral_constant<int, (kStages - 2) * kCopies>());
-  Ops h0, h1;
+      for (int c = 0; c < kCopies; ++c) issue(t * kBKk, t, c);
+    wait_barrier(std::integral_constant<int, 0>());
 #pragma unroll
-  for (int p = 0; p < 6; ++p) read_pair(buf[0], 0, p, h0);
-  int st = 0;
-  for (int64_t t = 0; t < nk; ++t) {
-    const int64_t k_nxt = min(t + kStages - 1, nk - 1) * kBKk;
-    const int old = (st + kStages - 1) & (kStages - 1), nx = (st + 1) & (kStages - 1);
-    half_step(h0, h1, buf[st], 1, k_nxt, old, 0);
-    wait_barrier(std::integral_constant<int, (kStages - 3) * kCopies + kCopies / 2>());
-    // (past the end: a stage that holds the last step again)
-    half_step(h1, h0, buf[nx], 0, k_nxt, old, kCopies / 2);
-    st = nx;
+    for (int t = 0; t < 2 * NK; ++t) {
+      Ops o;
+#pragma unroll
+      for (int p = 0; p < 6; ++p) read_pair(buf + t / 2 * kStage, t & 1, p, o);
+#pragma unroll
+      for (int q = 0; q < 8; ++q)
+        acc[(q >> 1) & 1][q & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(o.a[q >> 2][(q >> 1) & 1], o.b[q >> 2][q & 1],
+                                                                          acc[(q >> 1) & 1][q & 1], 0, 0, 0);
+    }
+  } else {
+    // Step t, whose first half's operands are in registers: multiply them while
+    // the second half's are read; wait until those reads and step t + 1's copies
+    // have landed (the younger ones stay in flight) and barrier; multiply the
+    // second half while step t + 1's first half is read.  The copies of step t +
+    // 3 (past the end, of the last step again: every step starts the same
+    // number) go into the stage step t - 1 left, which every wave had read by
+    // that step's barrier.  One wave per SIMD: the matrix pipe works through the
+    // reads and the barrier.
+    const int64_t nk = d.k / kBKk;
+#pragma unroll
+    for (int u = 0; u < kStages - 1; ++u)
+#pragma unroll
+      for (int c = 0; c < kCopies; ++c) issue(min((int64_t)u, nk - 1) * kBKk, u, c);
+    wait_barrier(std::integral_constant<int, (kStages - 2) * kCopies>());
+    Ops h0, h1;
+#pragma unroll
+    for (int p = 0; p < 6; ++p) read_pair(buf, 0, p, h0);
+    int st = 0;
+    for (int64_t t = 0; t < nk; ++t) {
+      const int64_t k_nxt = min(t + kStages - 1, nk - 1) * kBKk;
+      const int old = (st + kStages - 1) & (kStages - 1), nx = (st + 1) & (kStages - 1);
+      half_step(h0, h1, buf + st * kStage, 1, k_nxt, old, 0);
+      wait_barrier(std::integral_constant<int, (kStages - 3) * kCopies + kCopies / 2>());
+      // (past the end: a stage that holds the last step again)
+      half_step(h1, h0, buf + nx * kStage, 0, k_nxt, old, kCopies / 2);
+      st = nx;
+    }
   }
   // no copy into LDS outlives the block
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 
   __syncthreads();  // and every wave is past its reads
   const int64_t col0 = n0 + wn;
-  store_block(reinterpret_cast<float*>(buf[wave]), lane, m0 + wm, col0, d.m, epi, epi.col8(col0 + 8 * (lane & 7)),
+  store_block(reinterpret_cast<float*>(buf + wave * kBlockLds), lane, m0 + wm, col0, d.m, epi, epi.col8(col0 + 8 * (lane & 7)),
               [&](int i, int j) { return acc[i][j]; });
 }
 
@@ -658,12 +682,16 @@ int super_block(int64_t n_tiles) {
 }
 
 // Launch C = A B (+ epilogue).  The kernel is chosen by the rounds of
-// workgroups (one per compute unit) each would take; times at K = 4096 on 256
-// compute units:
+// workgroups (one per compute unit) each would take; times at K = 4096 (the order
+// is the same from K = 192 to 8192) on 256 compute units:
 // * few rows: one round of 64 x 64 skinny tiles (M = 256, N = 4096: 26 us, the
 //   128 x 128 kernel 28; M = 128, N = 12 288, two rounds: 50 against 29), and any
 //   N while one row tile of up to 32 rows holds M, where a second round still
 //   only reads B (M = 16, N = 12 288: 17.5 us against 28);
+// * K = 64 or 128: the 128 x 128 kernel that copies all of K at once, two
+//   workgroups a unit (M = 4096, N = 6144: 17.7 us against 27.1 with the larger
+//   tile at K = 64, 20.4 against 29.6 at 128; M = 1000, N = 4096: 6.6 against 7.4
+//   and 7.2 against 7.8 with the four stages);
 // * a full round of 256 x 256 tiles takes as long as 2.75 rounds of 128 x 128
 //   (78 us against 28), so those are used unless the larger tile saves more
 //   rounds than that (M = 1000: N = 4096 37 us against 79, N = 12 288 108
@@ -688,7 +716,7 @@ focus_status launch_gemm(const focus_gemm_desc& d, const Epi& epi, focus_stream_
   const int64_t m_tiles = focus::ceil_div(d.m, kBM), n_tiles = d.n / kBN;
   const int64_t m_tiles2 = focus::ceil_div(d.m, kBM2), n_tiles2 = d.n / kBN2;
   const int64_t rounds = focus::ceil_div(m_tiles * n_tiles, cus), rounds2 = focus::ceil_div(m_tiles2 * n_tiles2, cus);
-  if (d.n % kBN2 == 0 && 11 * rounds2 <= 4 * rounds) {
+  if (d.n % kBN2 == 0 && d.k > 2 * kBKk && 11 * rounds2 <= 4 * rounds) {
     const int sbw = super_block(n_tiles2);
     const int64_t blocks = m_tiles2 * n_tiles2;
     if (blocks > INT32_MAX) return FOCUS_E_SHAPE;
@@ -696,7 +724,13 @@ focus_status launch_gemm(const focus_gemm_desc& d, const Epi& epi, focus_stream_
   } else {
     const int64_t blocks = focus::ceil_div(m_tiles * n_tiles, focus::kXcds) * focus::kXcds;
     if (blocks > INT32_MAX) return FOCUS_E_SHAPE;
-    hipLaunchKernelGGL(gemm_bf16<Epi>, dim3((uint32_t)blocks), dim3(kThreads), 0, s, d, m_tiles, epi);
+    const dim3 grid((uint32_t)blocks), block(kThreads);
+    if (d.k == kBKk)
+      hipLaunchKernelGGL((gemm_bf16<Epi, 1>), grid, block, 0, s, d, m_tiles, epi);
+    else if (d.k == 2 * kBKk)
+      hipLaunchKernelGGL((gemm_bf16<Epi, 2>), grid, block, 0, s, d, m_tiles, epi);
+    else
+      hipLaunchKernelGGL(gemm_bf16<Epi>, grid, block, 0, s, d, m_tiles, epi);
   }
   return focus::launch_status();
 }

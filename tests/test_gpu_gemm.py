@@ -38,26 +38,29 @@ def test_gemm_matches_float64(m, n, k, out_dtype):
 @pytest.mark.parametrize("m,n,k", [(15, 128, 64), (16, 128, 576), (17, 256, 128), (32, 384, 64), (33, 128, 192),
                                    (65, 640, 64), (200, 12288, 128), (129, 16384, 64), (1025, 4224, 192),
                                    (2100, 4096, 64), (2100, 4352, 192), (4000, 2560, 128), (300, 32768, 192),
-                                   (2100, 4096, 192), (700, 6144, 192)])
+                                   (2100, 4096, 192), (4000, 2560, 256), (700, 6144, 192), (700, 6144, 128),
+                                   (130, 16384, 128)])
 def test_gemm_kernel_edges(m, n, k):
     """Each kernel of the dispatch at its edges: row tiles of 16, 32 and 64 (one
     and several), fewer k-steps than waves, the 128 x 128 tile over several
     rounds, the 256 x 256 tile with whole and partial groups of row stripes, in
     super blocks (N / 256 = 16, 10) and without (17).  Gathered rows in reverse,
-    C at a 2-byte-odd column offset so that no row is 16-byte aligned, and
-    nothing written around it.  float32 sums of k products in any order: as above."""
+    C at a column offset of two in a wider buffer (n + 6: some rows 16-byte
+    aligned, some not; n + 8: none), and nothing written around it.  float32 sums
+    of k products in any order: as above."""
     announce(f"gemm kernels m={m} n={n} k={k}")
     a = fw.randn((m + 3, k), "bf16", m + k, DEV)
     b = fw.randn((k, n), "bf16", n + 9, DEV)
     idx = torch.arange(m + 2, 2, -1, device=DEV)
     ref = a.float()[idx] @ b.float()
     for dt, tol in ((torch.float32, 1e-5), (torch.bfloat16, 5e-3)):
-        buf = torch.full((m + 1, n + 6), 7.0, dtype=dt, device=DEV)
-        F.focus_gemm(a, b, out=buf[:m, 2:2 + n], a_rows=idx)
         whole = F.focus_gemm(a, b, out_dtype=dt, a_rows=idx)
-        torch.cuda.synchronize()
-        assert torch.equal(buf[:m, 2:2 + n], whole)
-        assert (buf[:, :2] == 7).all() and (buf[:, 2 + n:] == 7).all() and (buf[m] == 7).all()
+        for pad in (6, 8):
+            buf = torch.full((m + 1, n + pad), 7.0, dtype=dt, device=DEV)
+            F.focus_gemm(a, b, out=buf[:m, 2:2 + n], a_rows=idx)
+            torch.cuda.synchronize()
+            assert torch.equal(buf[:m, 2:2 + n], whole)
+            assert (buf[:, :2] == 7).all() and (buf[:, 2 + n:] == 7).all() and (buf[m] == 7).all()
         assert float((whole.float() - ref).norm() / ref.norm()) <= tol
 
 
