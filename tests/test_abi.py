@@ -9,6 +9,7 @@ import re
 
 import numpy as np
 import pytest
+import torch
 
 import focus_workloads as fw
 import paper_2511_14694_amd as F
@@ -257,3 +258,92 @@ def test_window_attn_workspace_key_split_formula():
     d.dtype = 0
     d.totals = F.focus_layout_plan([100], 50, None, 10)
     assert ws() == 0                                   # two key tiles: nothing to split
+
+
+class _Recorder:
+    """Stands in for the library: keeps every call's descriptor, launches nothing."""
+
+    def __init__(self):
+        self.calls = {}
+
+    def __getattr__(self, name):
+        def call(d, *rest):
+            self.calls[name] = d._obj
+            return 48 if name.endswith("_workspace") else 0
+        return call
+
+
+def _check_fields(d, want):
+    """Every field of d by name: want's entry (a tensor stands for its address), for
+    all fields the struct has."""
+    assert set(want) == {n for n, *_ in d._fields_}, "a field without a value here"
+    for name, x in want.items():
+        x = x.data_ptr() if torch.is_tensor(x) else x
+        got = getattr(d, name)
+        if name == "totals":
+            got, x = got.as_dict(), x.as_dict()
+        assert got == x, (name, got, x)
+
+
+def test_descriptors_filled_by_position(monkeypatch):
+    """The binding fills these descriptors by position: each field holds what its
+    name says, all values different."""
+    rec = _Recorder()
+    monkeypatch.setattr(F, "lib", lambda: rec)
+    stream = type("Stream", (), {"cuda_stream": 1})()
+    monkeypatch.setattr(F, "_scratch", lambda n, device, s: torch.empty(n, dtype=torch.uint8))
+    bf, i32, i64 = torch.bfloat16, torch.int32, torch.int64
+    t = lambda *s, dt=bf: torch.zeros(*s, dtype=dt)
+    H, Hkv, D, B = 6, 3, 64, 2
+    tot = _abi.LayoutTotals(*range(11, 18))
+    names = F.WINDOW_FIELDS + F.TOKEN_FIELDS + ("sum_tok",)
+    kmer, ids, err = t(9, dt=i32), t(5, dt=i32), t(1, dt=i32)
+    lay = F.Layout(tot, B, 100, {n: t(9, dt=i64) for n in names}, kmer, 7)
+    q, k, v = t(20, H, D), t(20, Hkv, D), t(20, Hkv, D)
+    ck, cv, clen = t(B, 31, Hkv, D), t(B, 31, Hkv, D), t(B, dt=i32)
+    o, lse = t(20, H, D), t(20, H, dt=torch.float32)
+
+    F.focus_compact_kv(lay, k, v, ck, cv, clen, win_ids=ids, kv_tok_base=8, err=err, stream=stream)
+    own = {n: lay[n] for n in ("win_seq", "win_nsum", "win_cache_off", "win_sum_off", "sum_tok")}
+    _check_fields(rec.calls["focus_compact_kv"], dict(
+        own, totals=tot, dtype=0, n_kv_heads=Hkv, head_dim=D, batch=B, n_win=5, win_ids=ids, k=k, v=v, kv_tok_base=8,
+        kv_rows=20, cache_k=ck, cache_v=cv, cache_cap=31, cache_len=clen, err=err))
+
+    ws = t(64, dt=i64)
+    own = {n: lay[n] for n in ("win_seq", "win_ntok", "win_cache_off", "win_tok_off")}
+    want = dict(own, totals=tot, dtype=0, n_heads=H, n_kv_heads=Hkv, head_dim=D, softmax_scale=0.5, mask=1, batch=B,
+                kmer_uniform=7, n_win=5, win_ids=ids, win_kmer=kmer, q=q, k=k, v=v, qkv_tok_base=8, qkv_rows=20,
+                cache_k=ck, cache_v=cv, cache_cap=31, o=o, lse=lse, workspace=ws, workspace_bytes=512, err=err)
+    kw = dict(o=o, lse=lse, win_ids=ids, qkv_tok_base=8, softmax_scale=0.5, mask=1, err=err, stream=stream)
+    F.focus_window_attn(lay, q, k, v, ck, cv, workspace=ws, **kw)
+    _check_fields(rec.calls["focus_window_attn"], want)
+    F.focus_window_attn(lay, q, k, v, **kw)             # no cache; scratch of its own
+    d = rec.calls["focus_window_attn"]
+    assert (d.cache_k, d.cache_v, d.cache_cap, d.workspace_bytes) == (None, None, 0, 48) and d.workspace
+
+    dq, kn, vn, kind = t(B, H, D), t(B, Hkv, D), t(B, Hkv, D), t(B, dt=torch.uint8)
+    wk, wv, wlen, do, dlse = t(B, 40, Hkv, D), t(B, 40, Hkv, D), t(B, dt=i32), t(B, H, D), t(B, H, dt=torch.float32)
+    want = dict(dtype=0, batch=B, n_heads=H, n_kv_heads=Hkv, head_dim=D, softmax_scale=0.25, split_keys=16, reserved=0,
+                q=dq, k_new=kn, v_new=vn, kind=kind, cache_k=ck, cache_v=cv, cache_cap=31, cache_len=clen, win_k=wk,
+                win_v=wv, win_cap=40, win_len=wlen, o=do, lse=dlse, workspace=ws, workspace_bytes=512, err=err)
+    args = (dq, kn, vn, kind, ck, cv, clen, wk, wv, wlen)
+    kw = dict(split_keys=16, softmax_scale=0.25, err=err, stream=stream)
+    F.focus_decode_step(*args, o=do, lse=dlse, workspace=ws, **kw)
+    _check_fields(rec.calls["focus_decode_step"], want)
+    F.focus_decode_step_noalloc(*args, do, dlse, **kw)
+    _check_fields(rec.calls["focus_decode_step_noalloc"], dict(want, workspace=None, workspace_bytes=0))
+
+    sched = F.DecodeSchedule(B, 100, t(B, 4, dt=i32), 7, device="cpu", err=err)
+    want = dict(batch=B, window_nt=100, kmer_uniform=7, kmer_stride=4, kmer=sched.kmer, win_index=sched.win_index,
+                bases_in_window=sched.bases_in_window, bases_in_kmer=sched.bases_in_kmer, kind=sched.kind,
+                summaries=sched.summaries, err=err)
+    tokens = t(B, dt=i32)
+    sched.start(tokens, stream=stream)
+    _check_fields(rec.calls["focus_decode_sched_start"], dict(want, tokens=tokens))
+    sched.next_kind(stream=stream)
+    _check_fields(rec.calls["focus_decode_next_kind"], dict(want, tokens=None))
+
+    a, b, c, rows = t(10, 72)[:, :64], t(64, 144)[:, :128], t(3, 160)[:, :128], torch.tensor([4, 2, 9])
+    F.focus_gemm(a, b, out=c, a_rows=rows, alpha=0.75, err=err, stream=stream)
+    _check_fields(rec.calls["focus_gemm"], dict(m=3, n=128, k=64, a=a, lda=72, a_rows=rows, a_nrows=10, b=b, ldb=144, c=c,
+                                                ldc=160, c_dtype=0, alpha=0.75, err=err))

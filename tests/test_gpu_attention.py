@@ -448,6 +448,30 @@ def test_f32_error_of_a_score_is_that_of_32_products(L, W, k, H, D):
     assert np.linalg.norm(to64(p.o) - o) <= 2.8e-7 * np.linalg.norm(o)
 
 
+@pytest.mark.parametrize("H,B", [(8, 65_600), (9, 58_321)])
+def test_f32_more_workgroups_than_one_grid_dimension(H, B):
+    """A little over 2^20 workgroups of 16 rows: the grid gets a second dimension,
+    most of whose last row has no item (H a multiple of the eight XCDs, and not)."""
+    announce(f"attn f32 2-D grid H={H} B={B}")
+    D, T = 64, 17
+    blocks = -(-B * H // 8) * 8 * 2
+    assert (1 << 20) < blocks < (1 << 20) + 4096
+    p = Prefill([16] * B, 16, np.full(B, 16, np.int32), H, 1, D, "f32", seed=70)
+    assert p.totals.n_tokens == B * T
+    vis = torch.ones(T, T, dtype=torch.bool, device=DEV).tril()
+    for b in range(0, B, 8192):
+        sl = slice(b * T, min(b + 8192, B) * T)
+        q = p.q[sl].double().view(-1, T, H, D).transpose(1, 2)
+        k, v = (x[sl].double().view(-1, 1, T, D) for x in (p.k, p.v))
+        s = torch.matmul(q, k.transpose(2, 3).contiguous()) * D ** -0.5
+        s.masked_fill_(~vis, -float("inf"))
+        o = torch.matmul(torch.softmax(s, -1), v).transpose(1, 2)
+        assert (p.o[sl].view(-1, T, H, D) - o).abs().max().item() <= 1e-5
+        assert (p.lse[sl].view(-1, T, H).transpose(1, 2) - torch.logsumexp(s, -1)).abs().max().item() <= 1e-5
+    del p
+    torch.cuda.empty_cache()
+
+
 @pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("W,k,seq", [
     (40, 8, [400]),          # one 45-row query tile: three waves of the tile without a row
@@ -479,3 +503,35 @@ def test_ct_blocks_computed_alone(W, k, n, D):
     ref = build_layout(seq, W, km)
     p = Prefill(seq, W, km, 8, 4, D, "bf16", seed=67)
     compare_windows(ref, p, range(ref["n_windows"]), [0, 3, 7], "ct blocks alone")
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("W,k,H", [(600, 6, 2), (1200, 6, 2)])   # one workgroup per item; keys split in three
+def test_ct_running_reference_jumps(W, k, H, D):
+    """Keys whose score is 2^13 times the one before, for some rows of every query
+    block: the running reference moves while the output accumulators hold
+    something that still counts (the other keys' V is about 1, these keys' -1: 1024
+    others weigh an eighth).  They lie in full cache tiles, on both sides of the
+    border to the window, in full window tiles and in sub-tiles of both parities of
+    the diagonal ones."""
+    announce(f"attn ct reference jumps W={W} k={k} D={D}")
+    seq = [3 * W]
+    km = np.full(3, k, np.int32)
+    ref = build_layout(seq, W, km)
+    p = Prefill(seq, W, km, H, 1, D, "bf16", seed=68, run=False)
+    t0, T, C = int(ref["win_tok_off"][2]), int(ref["win_ntok"][2]), int(ref["win_cache_off"][2])
+    toks = list(A.cache_token_indices(ref, 2)[[100, C - 1]])
+    toks += [t0 + r for r in (0, 37, 261, 296, 331, 353, 386, 426, 456, 511, T - 30)]
+    p.v.mul_(0.3).add_(1.0)
+    p.q.mul_(0.1)
+    p.q[:, :, 0] = 0.0
+    p.q[0::3, 0, 0] = 1.0            # every block, some rows
+    p.q[t0 + 300:, 1, 0] = 1.0       # whole blocks from inside a tile on
+    p.k[:, :, 0] = 0.0
+    for i, t in enumerate(toks):     # 13 more in the base-2 exponent each
+        p.k[t, :, 0] = 13.0 * (i + 1) * D ** 0.5 * np.log(2.0)
+        p.v[t] -= 2.0
+    F.focus_compact_kv(p.lay, p.k, p.v, p.ck, p.cv, p.clen)
+    assert (F.focus_window_attn_workspace(p.lay, p.q, p.k, p.v, p.ck, p.cv) > 0) == (W == 1200)
+    p.o, p.lse = p.attn()
+    compare_windows(ref, p, [2], list(range(H)), "reference jumps")

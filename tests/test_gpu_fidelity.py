@@ -100,7 +100,8 @@ def test_empty_and_bounds():
     _check(mean[0].cpu().numpy().astype(np.float64), ref[:4].mean(0), "mean of a valid sequence")
 
 
-@pytest.mark.parametrize("cu", [[0, 2047, 4096], [1, 3, 4000, 9001], [0, 0, 5001, 5001, 8191], [5, 130_003]])
+@pytest.mark.parametrize("cu", [[0, 2047, 4096], [1, 3, 4000, 9001], [0, 0, 5001, 5001, 8191], [5, 130_003],
+                                [2, 6, 4102, 9000]])
 def test_sequence_means_split(cu):
     """Means of sequences that start at every 16-byte phase of the output rows,
     empty, shorter and longer than a split; with and without the split, against

@@ -91,6 +91,48 @@ def test_window_by_window_equals_whole_layout():
     assert torch.equal(ck, ck2) and torch.equal(cv, cv2)
 
 
+@pytest.mark.parametrize("d", [64, 128, 192])
+def test_whole_layout_and_windows_through_different_kernels(d):
+    """d = 192: the whole layout takes the 256 x 256 tiles (the larger tile saves
+    more than 2.75 rounds of workgroups a round), a window alone the 128 x 128 ones:
+    Q, K, V and the summary rows written straight to the cache are the same bits,
+    with a ragged row tail, and equal the oracle's and a compaction's.  d = 64 and
+    128: the kernel that copies all of K at once."""
+    seq, W, H, Hkv, D = [2950, 1203], 1000, 32, 8, 128
+    announce(f"qkv project across kernels d={d}")
+    km, tot, lay, hid, w = _setup(seq, W, None, H, Hkv, D, d, 47)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    rounds = lambda m, t: -(-(-(-m // t) * (6144 // t)) // cus)   # noqa: E731
+    ref = build_layout(seq, W, km)
+    longest = int(ref["win_ntok"].max())
+    assert 11 * rounds(tot.n_tokens, 256) <= 4 * rounds(tot.n_tokens, 128) and tot.n_tokens % 256
+    assert 11 * rounds(longest, 256) > 4 * rounds(longest, 128)
+    cap = max(tot.max_cache_per_seq, 1)
+    ck = torch.zeros(len(seq), cap, Hkv, D, dtype=torch.bfloat16, device=DEV)
+    cv = torch.zeros_like(ck)
+    clen = torch.zeros(len(seq), dtype=torch.int32, device=DEV)
+    err = torch.zeros(1, dtype=torch.int32, device=DEV)
+    q, k, v = F.focus_qkv_project(lay, hid, w, H, Hkv, 10000.0, cache_k=ck, cache_v=cv, cache_len=clen, err=err)
+    ck2, cv2, clen2 = torch.zeros_like(ck), torch.zeros_like(cv), torch.zeros_like(clen)
+    q2, k2, v2 = torch.empty_like(q), torch.empty_like(k), torch.empty_like(v)
+    for x in range(ref["n_windows"]):
+        t0 = int(ref["win_tok_off"][x])
+        sl = slice(t0, t0 + int(ref["win_ntok"][x]))
+        q2[sl], k2[sl], v2[sl] = F.focus_qkv_project(lay, hid[sl].contiguous(), w, H, Hkv, 10000.0, tok_base=t0,
+                                                     cache_k=ck2, cache_v=cv2, cache_len=clen2, err=err)
+    ck3, cv3, clen3 = torch.zeros_like(ck), torch.zeros_like(cv), torch.zeros_like(clen)
+    F.focus_compact_kv(lay, k, v, ck3, cv3, clen3)
+    torch.cuda.synchronize()
+    assert int(err.item()) == 0
+    for x, y, z in ((q, q2, q), (k, k2, k), (v, v2, v), (ck, ck2, ck3), (cv, cv2, cv3), (clen, clen2, clen3)):
+        assert torch.equal(x, y) and torch.equal(x, z)
+    rows = np.unique(np.concatenate([np.arange(0, tot.n_tokens, 37), np.arange(tot.n_tokens - 40, tot.n_tokens)]))
+    fetch = lambda r: to64(hid[torch.as_tensor(np.asarray(r, np.int64), device=DEV)])   # noqa: E731
+    idx = torch.as_tensor(rows, device=DEV)
+    for got, want, name in zip((q, k, v), P.qkv_project(ref, fetch, to64(w), H, Hkv, 10000.0, store_bf16=True, rows=rows), "qkv"):
+        assert_parity(to64(got[idx]), want, "bf16", name)
+
+
 def test_evo2_scale_projection_1mb_sampled():
     w_ = fw.WORKLOADS["prefill_1mb"]
     H, Hkv, D, d = w_.heads, w_.kv_heads, w_.head_dim, 4096

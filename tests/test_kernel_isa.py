@@ -1,4 +1,4 @@
-"""Checks on the gfx950 assembly of the k-mer-local window attention (attn_kl).
+"""Checks on the gfx950 assembly of the window attentions (attn_kl, attn_ct).
 
 attn_kl loads the next query tile's Q with inline-assembly global loads that
 it does not wait for at once: the registers are written when the loads land,
@@ -167,3 +167,59 @@ def test_ct_accumulators_touched_only_behind_wait_states(asm, name):
             assert not pending, s
     blocks += close()
     assert blocks >= 12, blocks  # four clean phases, eight masked ones
+
+
+def _sets(text):
+    """Registers of an operand list, as names (v1, a7)."""
+    out = set()
+    for kind, lo, hi in re.findall(r"\b([va])\[(\d+):(\d+)\]", text):
+        out |= {f"{kind}{x}" for x in range(int(lo), int(hi) + 1)}
+    out |= {m.group(0) for m in re.finditer(r"\b[va]\d+\b", text)}
+    return out
+
+
+@pytest.mark.parametrize("name", CT_KERNELS)
+def test_ct_output_products_read_settled_registers(asm, name):
+    """An inline-assembly MFMA gets no compiler wait states: a vector instruction's
+    result (a probability, an operand copied by the register allocator, an
+    accumulator written back) may be its source only from the third instruction on.
+    Checked against the two instructions before every such MFMA along all paths."""
+    start, end = _body(asm, name)
+    code, label_at = [], {}      # instructions; label -> index of the next one
+    for line in asm[start:end]:
+        s = line.split(";")[0].strip()
+        if s.endswith(":"):
+            label_at[s[:-1]] = len(code)
+        elif s and not s.startswith("."):
+            code.append(s)
+    jumps = {}                   # index -> branches that lead there
+    for i, s in enumerate(code):
+        if s.startswith(("s_branch", "s_cbranch")):
+            jumps.setdefault(label_at[s.split()[1]], []).append(i)
+
+    def writers(i, left):
+        """Vector instructions that end fewer than `left` wait states before code[i]."""
+        found = []
+        before = list(jumps.get(i, []))
+        if i > 0 and not code[i - 1].startswith(("s_branch", "s_endpgm", "s_setpc")):
+            before.append(i - 1)
+        for j in before:
+            s = code[j]
+            if s.startswith("v_") and not s.startswith("v_mfma"):
+                found.append(s)
+            states = int(s.split()[1], 0) + 1 if s.startswith("s_nop") else 1
+            if left > states:
+                found += writers(j, left - states)
+        return found
+
+    seen = 0
+    for i, s in enumerate(code):
+        if not (s.startswith("v_mfma") and s.split()[1].startswith("a[")):
+            continue
+        seen += 1
+        read = _sets(s.split(None, 1)[1])
+        for w in writers(i, 2):
+            ops = w.split(None, 1)[1]
+            dst = _sets(ops.split(",")[0]) | (_sets(ops) if "swap" in w.split()[0] else set())
+            assert not dst & read, (w, s)
+    assert seen >= 64
