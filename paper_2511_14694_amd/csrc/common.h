@@ -60,6 +60,18 @@ __device__ inline uint32_t pack_bf16x2(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, r);
 }
 
+// 16 bytes per lane from src to LDS byte lds + 16 lane (one wave: 1 KB), not
+// tracked by the compiler; lds goes in M0, which it writes just before, so the
+// copy waits one cycle for it (s_nop 0).
+__device__ __forceinline__ void copy_to_lds(const void* src, uint32_t lds) {
+  asm volatile(
+      "s_nop 0\n\t"
+      "global_load_lds_dwordx4 %0, off"
+      :
+      : "v"(src), "{m0}"(lds)
+      : "memory");
+}
+
 // Cross-lane sums inside aligned groups of 4 / 8 lanes (DPP, no LDS traffic).
 __device__ inline float dpp_xor1(float x) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0xB1, 0xF, 0xF, false));

@@ -25,12 +25,12 @@ namespace {
 
 using focus::bf16x4;
 using focus::bf16x8;
+using focus::copy_to_lds;
 using focus::f32x16;
 using focus::f32x4;
 using focus::u32x4;
 
 typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
-typedef __attribute__((address_space(3))) void lds_void;
 
 constexpr int kBM = 128, kBN = 128, kBKk = 64;   // C tile, K step
 constexpr int kThreads = 256;
@@ -194,20 +194,10 @@ struct QkvEpi {
   }
 };
 
-// Copies and waits of the 128 x 128 kernel: K advances 64 at a time through
-// four LDS stages, copies three steps ahead.  The copies are inline assembly (16
-// bytes per lane from src to LDS byte lds + 16 lane; lds goes in M0, written
-// just before, so the copy waits one cycle for it), so the compiler puts no
-// wait of its own in front of the LDS reads; the kernel's wait and barrier that
-// close each step order every read after the copies it needs.
-__device__ __forceinline__ void copy_to_lds(const void* src, uint32_t lds) {
-  asm volatile(
-      "s_nop 0\n\t"
-      "global_load_lds_dwordx4 %0, off"
-      :
-      : "v"(src), "{m0}"(lds)
-      : "memory");
-}
+// Copies and waits of both tiled kernels: K advances through four LDS stages,
+// copies three steps ahead.  The copies are inline assembly (focus::copy_to_lds), so
+// the compiler puts no wait of its own in front of the LDS reads; the kernel's wait
+// and barrier that close each step order every read after the copies it needs.
 
 // Stores 64 x 64 results of one wave (get(i, j) = the f32x16 of its 32 x 32
 // block i, j: element v is row 8 (v / 4) + 4 g + v % 4, column l32) at C[row0 ..][col0 ..]

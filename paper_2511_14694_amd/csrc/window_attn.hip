@@ -60,6 +60,7 @@ namespace {
 
 using focus::bf16x4;
 using focus::bf16x8;
+using focus::copy_to_lds;
 using focus::f32x16;
 using focus::f32x4;
 using focus::u32x4;
@@ -515,23 +516,11 @@ __global__ __launch_bounds__(64 * W, W == 1 ? 1 : 2) void attn_bf16(focus_attn_d
 // ------------------------------------------------- bf16 MFMA, k-mer-local
 
 // The k-mer-local kernel below issues its global -> LDS copies as inline
-// assembly, so the compiler does not track them: with the compiler-visible
-// copy in this loop's control flow it conservatively waits for every copy in
-// flight before a step's LDS reads, which would leave one tile in flight
-// instead of three.  The kernel's own waits (a vmcnt wait and a barrier that
+// assembly (focus::copy_to_lds), so the compiler does not track them: with the
+// compiler-visible copy in this loop's control flow it conservatively waits for
+// every copy in flight before a step's LDS reads, which would leave one tile in
+// flight instead of three.  The kernel's own waits (a vmcnt wait and a barrier that
 // close each step) order every LDS read after the copies it needs.
-//
-// 16 bytes per lane from src to LDS byte lds + 16 lane (one wave: 1 KB); lds
-// goes in M0, which the compiler writes just before, so the copy waits one
-// cycle for it (s_nop 0).
-__device__ __forceinline__ void copy_to_lds(const void* src, uint32_t lds) {
-  asm volatile(
-      "s_nop 0\n\t"
-      "global_load_lds_dwordx4 %0, off"
-      :
-      : "v"(src), "{m0}"(lds)
-      : "memory");
-}
 __device__ __forceinline__ uint32_t lds_addr(const char* p) {
   typedef const __attribute__((address_space(3))) char lds_char;
   return (uint32_t)(uintptr_t)(lds_char*)p;
