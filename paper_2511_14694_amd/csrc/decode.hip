@@ -26,7 +26,6 @@
 
 #include <algorithm>
 #include <mutex>
-#include <type_traits>
 
 namespace {
 
@@ -152,100 +151,111 @@ __global__ __launch_bounds__(kThreads) void decode_partial(focus_decode_desc d, 
   const uint4* vw = reinterpret_cast<const uint4*>(d.win_v) + (int64_t)b * d.win_cap * row_u4 + my_u4;
 
   float m = kMinit, l = 0.f;
-  auto attend = [&](auto careful) __attribute__((always_inline)) {
-    constexpr bool kCareful = decltype(careful)::value;
-    if (own) {
-      // The step's row is the first key of the running softmax; one head of each
-      // K/V group stores the pieces its threads hold.
-      const int64_t src = (int64_t)b * row_u4 + my_u4;
-      uint4 kr[kU4], vr[kU4];
+  if (own) {
+    // The step's row is the first key of the running softmax; one head of each
+    // K/V group stores the pieces its threads hold.
+    const int64_t src = (int64_t)b * row_u4 + my_u4;
+    uint4 kr[kU4], vr[kU4];
+#pragma unroll
+    for (int i = 0; i < kU4; ++i) {
+      kr[i] = reinterpret_cast<const uint4*>(d.k_new)[src + i];
+      vr[i] = reinterpret_cast<const uint4*>(d.v_new)[src + i];
+    }
+    if (h % (H / Hkv) == 0) {
+      uint4* dk = reinterpret_cast<uint4*>(ap.summary ? d.cache_k : d.win_k);
+      uint4* dv = reinterpret_cast<uint4*>(ap.summary ? d.cache_v : d.win_v);
+      const int64_t dst = ((int64_t)b * (ap.summary ? d.cache_cap : d.win_cap) + ap.row) * row_u4 + my_u4;
 #pragma unroll
       for (int i = 0; i < kU4; ++i) {
-        kr[i] = reinterpret_cast<const uint4*>(d.k_new)[src + i];
-        vr[i] = reinterpret_cast<const uint4*>(d.v_new)[src + i];
+        dk[dst + i] = kr[i];
+        dv[dst + i] = vr[i];
       }
-      if (!kCareful && h % (H / Hkv) == 0) {
-        uint4* dk = reinterpret_cast<uint4*>(ap.summary ? d.cache_k : d.win_k);
-        uint4* dv = reinterpret_cast<uint4*>(ap.summary ? d.cache_v : d.win_v);
-        const int64_t dst = ((int64_t)b * (ap.summary ? d.cache_cap : d.win_cap) + ap.row) * row_u4 + my_u4;
+    }
+    float kx[kEpt];
+    Elt<T>::unpack(kr, kx);
+    Elt<T>::unpack(vr, o);
+    float acc = 0.f;
 #pragma unroll
-        for (int i = 0; i < kU4; ++i) {
-          dk[dst + i] = kr[i];
-          dv[dst + i] = vr[i];
-        }
+    for (int e = 0; e < kEpt; ++e) acc = fmaf(q[e], kx[e], acc);
+    // (against the finite start: a score of -inf has weight 0, as in the chunks)
+    const float sn = head_sum<TPH>(acc);
+    m = fmaxf(m, sn);
+    l = __builtin_amdgcn_exp2f(sn - m);
+#pragma unroll
+    for (int e = 0; e < kEpt; ++e) o[e] *= l;
+  }
+  for (int j0 = jb; j0 < je; j0 += kChunk) {
+    uint4 kr[kChunk][kU4], vr[kChunk][kU4];
+#pragma unroll
+    for (int u = 0; u < kChunk; ++u) {
+      const int j = min(j0 + u, je - 1);
+      const uint4* kp = j < clen ? kc + (int64_t)j * row_u4 : kw + (int64_t)(j - clen) * row_u4;
+      const uint4* vp = j < clen ? vc + (int64_t)j * row_u4 : vw + (int64_t)(j - clen) * row_u4;
+#pragma unroll
+      for (int i = 0; i < kU4; ++i) {
+        kr[u][i] = kp[i];
+        vr[u][i] = vp[i];
       }
+    }
+    float s[kChunk];
+#pragma unroll
+    for (int u = 0; u < kChunk; ++u) {
       float kx[kEpt];
-      Elt<T>::unpack(kr, kx);
-      Elt<T>::unpack(vr, o);
+      Elt<T>::unpack(kr[u], kx);
       float acc = 0.f;
 #pragma unroll
       for (int e = 0; e < kEpt; ++e) acc = fmaf(q[e], kx[e], acc);
-      // (against the finite start: a score of -inf has weight 0, as in the chunks)
-      const float sn = head_sum<TPH>(acc);
-      m = fmaxf(m, sn);
-      l = __builtin_amdgcn_exp2f(sn - m);
-#pragma unroll
-      for (int e = 0; e < kEpt; ++e) o[e] *= l;
+      s[u] = head_sum<TPH>(acc);
+      if (j0 + u >= je) s[u] = -INFINITY;
     }
-    for (int j0 = jb; j0 < je; j0 += kChunk) {
-      uint4 kr[kChunk][kU4], vr[kChunk][kU4];
+    float mx = s[0];
 #pragma unroll
-      for (int u = 0; u < kChunk; ++u) {
-        const int j = min(j0 + u, je - 1);
-        const uint4* kp = j < clen ? kc + (int64_t)j * row_u4 : kw + (int64_t)(j - clen) * row_u4;
-        const uint4* vp = j < clen ? vc + (int64_t)j * row_u4 : vw + (int64_t)(j - clen) * row_u4;
+    for (int u = 1; u < kChunk; ++u) mx = fmaxf(mx, s[u]);
+    const float m_new = fmaxf(m, mx);
+    const float alpha = __builtin_amdgcn_exp2f(m - m_new);
+    l *= alpha;
 #pragma unroll
-        for (int i = 0; i < kU4; ++i) {
-          kr[u][i] = kp[i];
-          vr[u][i] = vp[i];
-        }
-      }
-      float s[kChunk];
+    for (int e = 0; e < kEpt; ++e) o[e] *= alpha;
+    m = m_new;
 #pragma unroll
-      for (int u = 0; u < kChunk; ++u) {
-        float kx[kEpt];
-        Elt<T>::unpack(kr[u], kx);
-        float acc = 0.f;
+    for (int u = 0; u < kChunk; ++u) {
+      const float p = __builtin_amdgcn_exp2f(s[u] - m);
+      l += p;
+      float vx[kEpt];
+      Elt<T>::unpack(vr[u], vx);
 #pragma unroll
-        for (int e = 0; e < kEpt; ++e) acc = fmaf(q[e], kx[e], acc);
-        s[u] = head_sum<TPH>(acc);
-        if (j0 + u >= je) s[u] = -INFINITY;
-      }
-      float mx = s[0];
-#pragma unroll
-      for (int u = 1; u < kChunk; ++u) mx = fmaxf(mx, s[u]);
-      const float m_new = fmaxf(m, mx);
-      const float alpha = __builtin_amdgcn_exp2f(m - m_new);
-      l *= alpha;
-#pragma unroll
-      for (int e = 0; e < kEpt; ++e) o[e] *= alpha;
-      m = m_new;
-#pragma unroll
-      for (int u = 0; u < kChunk; ++u) {
-        const float p = __builtin_amdgcn_exp2f(s[u] - m);
-        l += p;
-        float vx[kEpt];
-        Elt<T>::unpack(vr[u], vx);
-#pragma unroll
-        for (int e = 0; e < kEpt; ++e)
-          if (!kCareful || j0 + u < je) o[e] = fmaf(p, vx[e], o[e]);
-      }
+      for (int e = 0; e < kEpt; ++e) o[e] = fmaf(p, vx[e], o[e]);
     }
-  };
-  attend(std::integral_constant<bool, false>());
+  }
   // Rows past the split's end repeat its last one with weight zero, and zero times
-  // an infinity in its V is a NaN: then once more, without them.  (Clearing the
-  // loaded rows instead took 2 to 8 % of a step.)
+  // an infinity in its V is a NaN.  A NaN that no score explains (l is a number) is
+  // what the split's keys have in that column that is not finite: the value, or a
+  // NaN where two differ.  (Keeping those rows out of the sums instead -- clearing
+  // what was loaded, or the sums again without them -- changed what the loop above
+  // has in flight: up to 37 % of a step.)
   if (je > jb && (je - jb) % kChunk != 0) {
     bool nan = false;
 #pragma unroll
     for (int e = 0; e < kEpt; ++e) nan |= o[e] != o[e];
     if (__builtin_expect(__any(nan), 0)) {
-      m = kMinit;
-      l = 0.f;
+      uint32_t x[kEpt] = {};
+      for (int j = jb; j < je + own; ++j) {
+        const uint4* vp = j < clen ? vc + (int64_t)j * row_u4 : vw + (int64_t)(j - clen) * row_u4;
+        if (j == je) vp = reinterpret_cast<const uint4*>(d.v_new) + (int64_t)b * row_u4 + my_u4;
+        uint4 r[kU4];
+        float v[kEpt];
 #pragma unroll
-      for (int e = 0; e < kEpt; ++e) o[e] = 0.f;
-      attend(std::integral_constant<bool, true>());
+        for (int i = 0; i < kU4; ++i) r[i] = vp[i];
+        Elt<T>::unpack(r, v);
+#pragma unroll
+        for (int e = 0; e < kEpt; ++e) {
+          const uint32_t a = __float_as_uint(v[e]);
+          if ((a & 0x7f800000u) == 0x7f800000u) x[e] = x[e] == 0 || x[e] == a ? a : 0x7fc00000u;
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < kEpt; ++e)
+        if (l == l && o[e] != o[e] && x[e]) o[e] = __uint_as_float(x[e]);
     }
   }
   const int64_t slot = ((int64_t)b * n_split + c) * H + h;
