@@ -464,9 +464,9 @@ typedef struct {
  * offsets fall outside [0, n_pos] get FOCUS_ERR_BOUNDS and a zero mean. */
 focus_status focus_fidelity(const focus_fidelity_desc* d, focus_stream_t stream);
 
-/* The same call with scratch for the sequence means: focus_fidelity gives each
- * sequence one workgroup, which reads only a fraction of what the device can;
- * with at least focus_fidelity_workspace(d) bytes (0 when it would not help),
+/* The same call with scratch for the sequence means: focus_fidelity gives a
+ * sequence at most one workgroup, which reads only a fraction of what the device
+ * can; with at least focus_fidelity_workspace(d) bytes (0 when it would not help),
  * 4-byte aligned, long sequences are split over several, merged by a second
  * kernel (the means differ by float32 rounding only).  With workspace NULL or
  * smaller it is focus_fidelity.  The scratch is in use until the call's kernels
@@ -541,7 +541,9 @@ focus_status focus_adapter_attn(const focus_adapter_desc* d, focus_stream_t stre
  *     out = A W_O                                  ([n_summaries, d_model])
  * hidden [n_tokens, d_model] (global token order); w_q [d_model, H D]; w_k, w_v
  * [d_model, H_kv D]; w_o [H D, d_model]; all bf16, row-major.  Intermediates
- * live in the caller's workspace (size from focus_adapter_layer_workspace).
+ * live in the caller's workspace (size from focus_adapter_layer_workspace).  As
+ * with focus_gemm, the bits of a summary's row may depend on how many summaries
+ * the layout has.
  * Requirements: d_model a multiple of 128 and of 64; H D and H_kv D multiples of
  * 128.  Errors: as the calls above. */
 typedef struct {
@@ -591,7 +593,10 @@ focus_status focus_adapter_layer(const focus_adapter_layer_desc* d, focus_stream
  * (device, int64) gathers rows of A, e.g. the hidden states of the summary
  * tokens (sum_tok of focus_layout).  C is bf16 (round to nearest even) or f32.
  * Requirements: k a multiple of 64, n a multiple of 128, lda and ldb multiples
- * of 8, A and B 16-byte aligned.  Errors: E_NULL, E_ARG, E_DTYPE,
+ * of 8, A and B 16-byte aligned.  The order in which a row's products are added
+ * may depend on m (few rows take a kernel that splits k), so a row's bits may
+ * differ by float32 rounding between calls of different m; focus_qkv_project's do
+ * not.  Errors: E_NULL, E_ARG, E_DTYPE,
  * E_UNSUPPORTED (k or n not a multiple of the tile), E_SHAPE, E_HIP.  A gathered
  * row outside [0, a_nrows) reads row 0 instead and sets FOCUS_ERR_BOUNDS. */
 typedef struct {

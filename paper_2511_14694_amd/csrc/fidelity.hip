@@ -345,7 +345,7 @@ __device__ inline float half_min(float x) { return -half_max(-x); }
 // * without the clip, both rows are taken in units of p's largest probability
 //   (p' = e_p^2, q' = (e_q s)^2 with s = sqrt(rq / rp)) and the sums scaled at
 //   the end: one product less per element.
-// Bound by the vector unit: 1 M x 512 bf16 with means 617 -> 584 us (one box)
+// Bound by the vector unit: 1 M x 512 bf16 with means 617 -> 584 us
 // against separate logarithms and scaled probabilities; eight positions per
 // half-wave with the next row prefetched took 7 % longer (fewer waves).
 template <typename T, int NPL, bool FULL>

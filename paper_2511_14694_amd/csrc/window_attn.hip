@@ -1004,7 +1004,7 @@ __device__ __forceinline__ float row_max(const f32x16& s) {
 // two waves per SIMD, which read every operand for one MFMA: 1 Mb 82.7 -> 78.3
 // ms, 32 kb dense 7.20 -> 6.66, 100 kb 2.14 -> 2.10, the ragged batch 12.5 -> 12.1,
 // 100 kb at head_dim 64 1.30 -> 1.15, windows of 512 5.5 -> 4.8, one window per
-// call 172 -> 162 us (one box).  A workgroup of 18 tiles takes 1.85 us a clean
+// call 172 -> 162 us (one device).  A workgroup of 18 tiles takes 1.85 us a clean
 // step, 2.08 a masked one, and about 9 us before, between and after.
 // A persistent form (one workgroup per compute unit over many items, the next
 // item's first tiles and Q on their way during the last steps) was slower: 1 Mb
